@@ -247,8 +247,7 @@ hipEvent_t prof_event(Ctx* c) {
 
 // Start a timed launch group; returns its index or -1 when profiling is off.
 int prof_begin(Ctx* c, int cls, int layer, int tile, const char* name, double flops, double bytes) {
-  if (!c || !c->prof_on) return -1;
-  Ctx::ProfEv ev{cls, layer, tile, name, flops, bytes, prof_event(c), prof_event(c)};
+    Ctx::ProfEv ev{cls, layer, tile, name, flops, bytes, prof_event(c), prof_event(c)};
   if (!ev.a || !ev.b || hipEventRecord(ev.a, c->stream) != hipSuccess) return -1;
   c->prof.push_back(ev);
   return (int)c->prof.size() - 1;
@@ -256,9 +255,11 @@ int prof_begin(Ctx* c, int cls, int layer, int tile, const char* name, double fl
 void prof_end(Ctx* c, int idx) {
   if (idx >= 0) (void)hipEventRecord(c->prof[idx].b, c->stream);
 }
+// (the record's arguments, names among them, are only evaluated while profiling)
+#define PROF_BEGIN(c, ...) ((c) && (c)->prof_on ? prof_begin(c, __VA_ARGS__) : -1)
 #define TIMED(cls, layer, tile, name, fl, by, expr)             \
   do {                                                          \
-    const int pi_ = prof_begin(c, cls, layer, tile, name, fl, by); \
+    const int pi_ = PROF_BEGIN(c, cls, layer, tile, name, fl, by); \
     LCHK(expr);                                \
     prof_end(c, pi_);                          \
   } while (0)
@@ -546,7 +547,7 @@ int launch_dgrad(int prec, const void* dy, const void* wd, void* dx, int N, int 
     } else if (feed) {
       *feed->ok = false;
     }
-    const int pi = prof_begin(c, RN18_K_CONV_DGRAD, layer, conv_gather_tile(prec, g), conv_gather_kernel_name(prec, g), 2.0 * g.M * creal * g.K, 0.0);
+    const int pi = PROF_BEGIN(c, RN18_K_CONV_DGRAD, layer, conv_gather_tile(prec, g), conv_gather_kernel_name(prec, g), 2.0 * g.M * creal * g.K, 0.0);
     const int r = conv_gather_launch(prec, g, st);
     prof_end(c, pi);
     return r;
@@ -599,7 +600,7 @@ int launch_dgrad(int prec, const void* dy, const void* wd, void* dx, int N, int 
     *feed->ok = false;
     for (int i = 0; i < np; ++i) ph4[i].bstats = nullptr;
   }
-  const int pi = prof_begin(c, RN18_K_CONV_DGRAD, layer, conv_gather_tile_multi(prec, ph4, np),
+  const int pi = PROF_BEGIN(c, RN18_K_CONV_DGRAD, layer, conv_gather_tile_multi(prec, ph4, np),
                             conv_gather_kernel_name_multi(prec, ph4, np),
                             flops, 0.0);
   const int r = conv_gather_launch_multi(prec, ph4, np, st);
@@ -623,7 +624,7 @@ int launch_wgrad_part(int prec, const void* dy, const void* x, float* wpart, int
   g.pix_per_split = pps;
   g.splits = splits;
   const double mpix = (double)N * Ho * Wo;
-  int pi = prof_begin(c, RN18_K_CONV_WGRAD, layer, conv_wgrad_tile(prec, Cout, g.Kcols), conv_wgrad_kernel_name_shape(prec, g),
+  int pi = PROF_BEGIN(c, RN18_K_CONV_WGRAD, layer, conv_wgrad_tile(prec, Cout, g.Kcols), conv_wgrad_kernel_name_shape(prec, g),
                       2.0 * Cout * (s2d ? 49 : k * k) * cin_real * mpix,
                       (double)splits * Cout * g.Kcols * 4);
   int r = conv_wgrad_launch(prec, g, st);
@@ -635,7 +636,7 @@ int launch_wgrad_part(int prec, const void* dy, const void* x, float* wpart, int
 int launch_wgrad_reduce(const float* wpart, int splits, int Cout, int k, int Cin, int cin_real, float* out, bool s2d,
                         hipStream_t st, Ctx* c = nullptr, int layer = -1) {
   const double kcols = (double)k * k * Cin;
-  const int pi = prof_begin(c, RN18_K_WGRAD_REDUCE, layer, 0, "wgrad_reduce_kernel", 0.0,
+  const int pi = PROF_BEGIN(c, RN18_K_WGRAD_REDUCE, layer, 0, "wgrad_reduce_kernel", 0.0,
                             ((double)splits + 1.0) * Cout * kcols * 4);
   const int r = wgrad_reduce_launch(wpart, splits, Cout, k * k, Cin, cin_real, out, s2d ? 1 : 0, st);
   prof_end(c, pi);

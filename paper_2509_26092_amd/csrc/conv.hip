@@ -32,6 +32,7 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <type_traits>
 
 namespace rn18 {
 
@@ -191,8 +192,8 @@ __device__ inline void bwd_partial_add(const ConvGather& g, const uint4& pk, uin
   }
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, bool UNI, bool RP>
-__device__ inline void gather_impl(const ConvGather& g) {
+template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, bool UNI>
+__global__ __launch_bounds__(64 * WGM * WGN) void conv_gather2_kernel(ConvGather g) {
   constexpr int NW = WGM * WGN, NT = 64 * NW;
   constexpr int VW = TT<T>::VW;
   constexpr int KT = 128 / (int)sizeof(T);
@@ -362,66 +363,6 @@ __device__ inline void gather_impl(const ConvGather& g) {
   const int S = (ks + 1) * S_all / ksplit - s_lo;
   const int arow0 = wm * WTM, brow0 = wn * WTN;
   const int sw = (lane >> 1) & 7;                 // (row / 2) % 8 of the operand rows
-  if constexpr (RP) {
-    // Register-prefetched loop: the operand fragments of stage s+1 are read
-    // from LDS while the MFMAs of stage s run from registers, and a ring
-    // buffer is refilled as soon as every wave has read it (before its
-    // MFMAs), so all STAGES buffers are in flight.
-    auto read_stage = [&](int s, uint4(&a)[2][FM], uint4(&b)[2][FN]) {
-      const uint4* As = smem + (s % STAGES) * STAGE_U4;
-      const uint4* Bs = As + BM * 8;
-#pragma unroll
-      for (int kg = 0; kg < 2; ++kg) {
-        const int slot = (kg * 4 + (lane >> 4)) ^ sw;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) a[kg][i] = As[(arow0 + i * 16 + (lane & 15)) * 8 + slot];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) b[kg][j] = Bs[(brow0 + j * 16 + (lane & 15)) * 8 + slot];
-      }
-    };
-    auto mma_regs = [&](const uint4(&a)[2][FM], const uint4(&b)[2][FN]) {
-#pragma unroll
-      for (int kg = 0; kg < 2; ++kg)
-#pragma unroll
-        for (int tt = 0; tt < Mma<T>::SUB; ++tt)
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) Mma<T>::run(acc[i][j], a[kg][i], b[kg][j], tt);
-    };
-    auto body = [&](int s, const uint4(&ac)[2][FM], const uint4(&bc)[2][FN], uint4(&an)[2][FM],
-                    uint4(&bn)[2][FN]) {
-      // stage s+1 must have landed; the stages after it may stay in flight
-      if (s + 1 < S) wait_stage<IPW>(min(STAGES - 2, S - 2 - s));
-      // this wave's reads of stage s are complete (s_waitcnt lgkmcnt(0))
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      barrier_only();
-      if (s + STAGES < S) {
-        if (UNI) issue_uni(s % STAGES);
-        else issue(s + STAGES, s % STAGES);
-      }
-      if (s + 1 < S) read_stage(s + 1, an, bn);
-      __builtin_amdgcn_sched_barrier(0);
-      mma_regs(ac, bc);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-#pragma unroll
-    for (int p = 0; p < STAGES; ++p)
-      if (p < S) {
-        if (UNI) issue_uni(p);
-        else issue(p, p);
-      }
-    uint4 a0[2][FM], b0[2][FN], a1[2][FM], b1[2][FN];
-    if (S > 0) {
-      wait_stage<IPW>(min(STAGES - 1, S - 1));
-      barrier_only();
-      read_stage(0, a0, b0);
-    }
-    for (int s = 0; s < S; s += 2) {
-      body(s, a0, b0, a1, b1);
-      if (s + 1 < S) body(s + 1, a1, b1, a0, b0);
-    }
-  } else {
 #pragma unroll
   for (int p = 0; p < STAGES - 1; ++p)
     if (p < S) {
@@ -458,7 +399,6 @@ __device__ inline void gather_impl(const ConvGather& g) {
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j) Mma<T>::run(acc[i][j], a[kg][i], b[kg][j], tt);
-  }
   }
   wait_vmcnt<0>();
   __syncthreads();
@@ -588,10 +528,6 @@ __device__ inline void gather_impl(const ConvGather& g) {
   }
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, bool UNI>
-__global__ __launch_bounds__(64 * WGM * WGN) void conv_gather2_kernel(ConvGather g) {
-  gather_impl<T, BM, BN, WGM, WGN, STAGES, UNI, false>(g);
-}
 // Split-K reduce: the ksplit fp32 partial tiles of a gather launch summed in
 // range order, then the gather epilogue on the sum (mode 0 store, 1
 // accumulate, 2 masked residual; storage rounding). With g.stats set, the BN
@@ -702,10 +638,699 @@ constexpr int gather_occupancy(int bm, int bn, int nw, int stages) {
   const int w = gather_blocks_per_cu(bm, bn, stages) * nw / 4;
   return w < 1 ? 1 : w > 8 ? 8 : w;
 }
-template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, bool UNI>
-__global__ __launch_bounds__(64 * WGM * WGN, gather_occupancy(BM, BN, WGM * WGN, STAGES)) void conv_gather_rp_kernel(
-    ConvGather g) {
-  gather_impl<T, BM, BN, WGM, WGN, STAGES, UNI, true>(g);
+// ---------------------------------------------------------------------------
+// Gather conv, half-stage pipelined. As above, with three changes.
+//
+// K loop: a stage is two K halves of 64 bytes per row. While the MFMAs of one
+// half run from registers, the operand fragments of the next half are read
+// from LDS between them (so the LDS pipe works beside the matrix pipe instead
+// of before it). Every wave has read the whole of stage s by the middle of its
+// MFMAs: there, after the only barrier of the stage, its ring buffer is
+// refilled with stage s + STAGES, so all STAGES buffers are in flight.
+//
+// Operand order: the weights are the first MFMA operand, so a lane's
+// accumulators are consecutive output channels of one pixel and the epilogue
+// stores 16-byte chunks straight from registers, without LDS. In 16-bit types
+// a chunk is 8 channels, two MFMA tiles wide: tiles 2p and 2p + 1 of a wave
+// take the weight rows 32 p + 8 (r / 4) + 4 (tile & 1) + r % 4 as their rows
+// r, so that their accumulators are channels 8 q .. 8 q + 3 and 8 q + 4 ..
+// 8 q + 7 of lane group q. Weight rows are swizzled in LDS by key(row) =
+// (row / 2) % 2 + 2 ((row / 8) % 4), which puts the 16 rows of such an operand
+// read on distinct 16-byte bank groups (fp32: consecutive rows, (row / 2) % 8
+// as for the pixels).
+//
+// Statistics: sums over a wave's pixels with DPP adds within the 16 lanes that
+// hold the same channels, then over the waves of a tile through LDS.
+//
+// Uniform row layout only (gather_uniform).
+// ---------------------------------------------------------------------------
+// Pixel rows of a stage in LDS: whole 8-row load instructions for every wave
+// (the rows past the tile are loaded as zeros and not read).
+constexpr int gather_rp_rows(int bm, int nw) { return (bm + 8 * nw - 1) / (8 * nw) * (8 * nw); }
+
+template <int CTRL>
+__device__ inline float dpp_add(float v) {
+  const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(float, o);
+}
+// Sum over each row of 16 lanes, in every lane: lane ^ 1, lane ^ 2, then the
+// mirrored lane of the half row and of the row.
+__device__ inline float row16_sum(float v) {
+  return dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int KW, int STAGES>
+__global__ __launch_bounds__(64 * WGM * WGN * KW, gather_occupancy(gather_rp_rows(BM, WGM * WGN * KW), BN, WGM * WGN * KW,
+                                                                   STAGES)) void conv_gather_rp_kernel(ConvGather g) {
+  constexpr int NW = WGM * WGN * KW, NT = 64 * NW;
+  constexpr int BMP = gather_rp_rows(BM, NW);      // pixel rows of a stage in LDS
+  constexpr int VW = TT<T>::VW;
+  constexpr int KT = 128 / (int)sizeof(T);
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  constexpr int FM = WTM / 16, FN = WTN / 16;
+  constexpr int AI = BMP / 8, BI = BN / 8;         // 8-row load instructions per stage
+  constexpr int UA = AI / NW, UB = BI / NW, IPW = UA + UB;
+  constexpr int STAGE_B = (BMP + BN) * 128;
+  constexpr int TPC = VW / 4;                      // MFMA tiles per 16-byte output chunk
+  constexpr int NC = FN / TPC;                     // output chunks per lane and pixel
+  static_assert((NW == 4 || NW == 8) && (KW == 1 || KW == 2), "4 or 8 waves");
+  static_assert(AI % NW == 0 && BI % NW == 0 && WTM % 16 == 0 && WTN % 16 == 0, "whole load instructions per wave");
+  static_assert(KW == 1 || WGM * WGN * FM * FN * 1024 <= STAGES * STAGE_B, "exchanged accumulators fit in the ring");
+  static_assert(FN % TPC == 0 && BN % 32 == 0, "whole output chunks");
+  static_assert(STAGES >= 2 && STAGES <= 5 && (STAGES - 1) * IPW < 64, "stages");
+  static_assert((BN + NW * WTN * 2) * 4 <= STAGES * STAGE_B, "statistics fit in the ring");
+  __shared__ uint4 smem[STAGES * STAGE_B / 16];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kx = wave / (WGM * WGN), wmn = wave - kx * (WGM * WGN);   // K half of this wave (KW == 2)
+  const int wm = wmn / WGN, wn = wmn % WGN;
+  const int tiles_n = (g.Cols + BN - 1) / BN;
+  // split-K: logical block = range * tiles + tile, so the tiles of one K
+  // range sit together on an XCD (they share operand rows of that range)
+  const int ksplit = g.ksplit > 1 ? g.ksplit : 1;
+  const int tiles = ((g.M + BM - 1) / BM) * tiles_n;
+  const int tk = xcd_remap(blockIdx.x, gridDim.x);
+  const int ks = ksplit > 1 ? tk / tiles : 0;
+  const int t = tk - ks * tiles;
+  const int tm = t / tiles_n;
+  const int m0 = tm * BM, n0 = (t - tm * tiles_n) * BN;
+  const int S_all = (g.K + KT - 1) / KT;
+  const int s_lo = ks * S_all / ksplit;            // this block's stages [s_lo, s_lo + S)
+  const int S = (ks + 1) * S_all / ksplit - s_lo;
+  const int HWm = g.Hm * g.Wm;
+  const int es = (int)sizeof(T);
+  const uint32_t smem_lds = lds_addr(smem);
+
+  // ---- loads. Load instruction u of this wave fills rows 8 (wave + NW u) ..
+  // + 7 of the stage (pixels, then weights); the lane's 16 bytes go to slot
+  // lane % 8 of row lane / 8. Byte offsets and tap-validity masks are fixed
+  // for the whole K loop, a stage adds the wave-uniform offset of its tap and
+  // channel block. With fewer channels than a row (Cin < KT) a row holds RT
+  // consecutive taps along w.
+  const int RT = g.Cin < KT ? KT / g.Cin : 1;
+  const int ntw_g = g.ntw / RT;
+  uint32_t uoff[IPW], umask[UA];
+  const i32x4_t rsA = buffer_rsrc(g.A, (uint32_t)((long)g.N * g.Hin * g.Win * g.Cin * es));
+  const i32x4_t rsB = buffer_rsrc(g.B, (uint32_t)((long)g.Cols * g.KHW * g.Cin * es));
+  {
+    const int c = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));       // pixel rows: key (row / 2) % 8
+    const int lane_px = (c * VW) / g.Cin;
+#pragma unroll
+    for (int u = 0; u < UA; ++u) {
+      const int r = (wave + NW * u) * 8 + (lane >> 3), m = m0 + r;
+      const bool ok = m < g.M && (BM == BMP || r < BM);
+      const int mm = ok ? m : 0;
+      const int n = (int)g.fd_hw.div(mm), rem = mm - n * HWm;
+      const int i = (int)g.fd_w.div(rem), jj = rem - i * g.Wm;
+      const int hb = i * g.is - g.ip, wb = jj * g.is - g.ip;
+      uint32_t vh = 0, vw = 0, msk = 0;
+      for (int th = 0; th < g.nth; ++th)
+        vh |= (unsigned)(hb + g.dh0 + th * g.dhs) < (unsigned)g.Hin ? 1u << th : 0u;
+      for (int tg = 0; tg < ntw_g; ++tg)
+        vw |= (unsigned)(wb + g.dw0 + (tg * RT + lane_px) * g.dws) < (unsigned)g.Win ? 1u << tg : 0u;
+      for (int th = 0; th < g.nth; ++th) msk |= (vh >> th) & 1u ? vw << (th * ntw_g) : 0u;
+      umask[u] = ok ? msk : 0u;
+      uoff[u] = (uint32_t)(((n * g.Hin + hb) * g.Win + wb) * g.Cin * es + c * 16);
+    }
+    const int cb = VW == 8 ? (lane & 7) ^ (((lane >> 4) & 1) | ((wave & 3) << 1)) : c;
+#pragma unroll
+    for (int u = UA; u < IPW; ++u) {
+      const int col = n0 + (wave + NW * u - AI) * 8 + (lane >> 3);
+      // (kOutOfRange stays out of range with any stage offset below 2^31)
+      uoff[u] = col < g.Cols ? (uint32_t)((long)col * g.KHW * g.Cin * es + cb * 16) : kOutOfRange;
+    }
+  }
+  // the next stage to issue: tap (th, tw group), tap index, channel block
+  int st_th, st_tw, st_ti, st_cb;
+  {
+    const int per_cb = g.nth * ntw_g;
+    st_cb = s_lo / per_cb;
+    st_ti = s_lo - st_cb * per_cb;
+    st_th = st_ti / ntw_g;
+    st_tw = st_ti - st_th * ntw_g;
+  }
+  // stage_begin fixes the wave-uniform parts of the next stage and its ring
+  // buffer, stage_load(u) issues load u of it. A stage that is not live (past
+  // the last one) reads nothing (its pixel rows are zeros, its weight rows the
+  // tensor's start) but counts as issued, so every wait count is a constant.
+  uint32_t ld_base = 0, ld_sa = 0, ld_sb = 0, ld_bit = 0;
+  auto stage_begin = [&](uint32_t ring, bool live) {
+    ld_base = smem_lds + ring;
+    const int dh = g.dh0 + st_th * g.dhs, dw = g.dw0 + st_tw * RT * g.dws;
+    const int wt = (g.wkh0 + st_th * g.wkhs) * g.KW + g.wkw0 + st_tw * RT * g.wkws;
+    ld_sa = (uint32_t)((dh * g.Win + dw) * g.Cin * es + st_cb * 128);
+    ld_sb = live ? (uint32_t)(wt * g.Cin * es + st_cb * 128) : 0u;
+    ld_bit = live ? 1u << st_ti : 0u;
+    // taps inner, channel blocks outer: consecutive stages of a channel block
+    // read input rows shifted by one tap, which L2 (and at times L1) still holds
+    ++st_ti;
+    if (++st_tw == ntw_g) {
+      st_tw = 0;
+      if (++st_th == g.nth) { st_th = 0; st_ti = 0; ++st_cb; }
+    }
+  };
+  auto stage_load = [&](int u) {
+    const uint32_t dst = ld_base + (uint32_t)((wave + NW * u) * 1024);
+    if (u < UA) lds_dma16_buf(umask[u] & ld_bit ? uoff[u] + ld_sa : kOutOfRange, rsA, dst);
+    else lds_dma16_buf(uoff[u] + ld_sb, rsB, dst);
+  };
+
+  // ---- operand fragments of half x of the stage at byte offset st of the ring
+  const int q4 = lane >> 4, l16 = lane & 15;
+  const int arow0 = wm * WTM, brow0 = wn * WTN;
+  const char* const sm = (const char*)smem;
+  const uint32_t la = (uint32_t)((arow0 + l16) * 128 + ((q4 ^ (l16 >> 1)) * 16));
+  const uint32_t lb = VW == 8 ? (uint32_t)((BMP + brow0 + 8 * (l16 >> 2) + (l16 & 3)) * 128 +
+                                           ((q4 ^ (((l16 >> 1) & 1) | ((l16 >> 2) << 1))) * 16))
+                              : (uint32_t)((BMP + brow0 + l16) * 128 + ((q4 ^ (l16 >> 1)) * 16));
+  constexpr int NF = FM + FN, NM = FM * FN * Mma<T>::SUB;
+  uint4 a0[FM], b0[FN], a1[FM], b1[FN];
+  // fragment f of a half: the FN weight fragments first, then the FM pixel ones
+  auto read_frag = [&](int f, uint32_t st, int x, uint4(&a)[FM], uint4(&b)[FN]) {
+    if (f < FN) {
+      const int row = VW == 8 ? (f >> 1) * 32 + (f & 1) * 4 : f * 16;
+      b[f] = *(const uint4*)(sm + ((st + lb) ^ (uint32_t)(64 * x)) + row * 128);
+    } else {
+      a[f - FN] = *(const uint4*)(sm + ((st + la) ^ (uint32_t)(64 * x)) + (f - FN) * 2048);
+    }
+  };
+  floatx4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // the MFMAs of one half, with extra(e), e < NP, spread between pairs of them
+  auto half = [&](const uint4(&a)[FM], const uint4(&b)[FN], auto np, auto&& extra) {
+    constexpr int NP = decltype(np)::value;
+#pragma unroll
+    for (int m = 0; m < NM; m += 2) {
+#pragma unroll
+      for (int e = 0; e < NP; ++e)
+        if (e * NM / NP >= m && e * NM / NP < m + 2) extra(e);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = m; k < m + 2 && k < NM; ++k) {
+        const int tt = k / (FM * FN), r = k % (FM * FN);
+        Mma<T>::run(acc[r / FN][r % FN], b[r % FN], a[r / FN], tt);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+#pragma unroll
+  for (int p = 0; p < STAGES; ++p) {
+    stage_begin((uint32_t)(p * STAGE_B), p < S);
+#pragma unroll
+    for (int u = 0; u < IPW; ++u) stage_load(u);
+  }
+  // reads and refill loads alternate while both last
+  auto read_or_load = [&](int e, uint32_t st, int x, uint4(&a)[FM], uint4(&b)[FN]) {
+    constexpr int MIN = NF < IPW ? NF : IPW;
+    const bool is_read = e < 2 * MIN ? e % 2 == 0 : NF > IPW;
+    const int k = e < 2 * MIN ? e / 2 : e - MIN;
+    if (is_read) read_frag(k, st, x, a, b);
+    else stage_load(k);
+  };
+  wait_vmcnt<(STAGES - 1) * IPW>();
+  barrier_only();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) read_frag(f, 0u, kx, a0, b0);
+  uint32_t st = 0;    // byte offset of stage s in the ring
+  // Stage s + 1 has landed (the stages after it may stay in flight) and this
+  // wave has read all it needs of stage s (lgkmcnt(0)); after the barrier so
+  // has everybody, and the ring buffer of stage s takes stage s + STAGES.
+  auto next_stage = [&](int s) {
+    wait_vmcnt<(STAGES - 2) * IPW>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    barrier_only();
+    stage_begin(st, s + STAGES < S);
+    st = st == (uint32_t)((STAGES - 1) * STAGE_B) ? 0u : st + (uint32_t)STAGE_B;
+  };
+  // (the fragments read after the last stage are not used)
+  if constexpr (KW == 1) {
+    for (int s = 0; s < S; ++s) {
+      half(a0, b0, std::integral_constant<int, NF>{}, [&](int f) { read_frag(f, st, 1, a1, b1); });
+      next_stage(s);
+      half(a1, b1, std::integral_constant<int, NF + IPW>{}, [&](int e) { read_or_load(e, st, 0, a0, b0); });
+    }
+  } else {
+    for (int s = 0; s < S; s += 2) {
+      next_stage(s);
+      half(a0, b0, std::integral_constant<int, NF + IPW>{}, [&](int e) { read_or_load(e, st, kx, a1, b1); });
+      if (s + 1 == S) break;
+      next_stage(s + 1);
+      half(a1, b1, std::integral_constant<int, NF + IPW>{}, [&](int e) { read_or_load(e, st, kx, a0, b0); });
+    }
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  if constexpr (KW == 2) {
+    // the two waves of a K pair exchange accumulators: the first finishes the
+    // first FM / 2 (rounded up) pixel rows of MFMA tiles, the second the rest
+    constexpr int H = (FM + 1) / 2;
+    floatx4_t* X = (floatx4_t*)smem + wmn * (FM * FN * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        if ((i < H) == (kx == 1)) X[(i * FN + j) * 64] = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        if ((i < H) == (kx == 0)) acc[i][j] += X[(i * FN + j) * 64];
+    __syncthreads();
+  }
+  // whether this wave finishes row i of MFMA tiles
+  auto mine = [&](int i) { return KW == 1 || (i < (FM + 1) / 2) == (kx == 0); };
+
+  // ---- epilogue: chunk p of pixel row i is channels col0 + p * 4 TPC * 4 ..
+  // + VW of pixel m0 + arow0 + 16 i + lane % 16
+  constexpr int CST = 16 * TPC;                    // channels between a lane's chunks
+  const int col0 = n0 + brow0 + q4 * VW;
+  if (ksplit > 1) {
+    // split-K: the raw fp32 tile of this K range, row m at m * Cols
+    float* __restrict__ P = g.part + (size_t)ks * g.M * g.Cols;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = m0 + arow0 + 16 * i + l16;
+      if (m >= g.M || !mine(i)) continue;
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int col = col0 + (j / TPC) * CST + (j % TPC) * 4;
+        if (col < g.Cols) *(floatx4_t*)(P + (size_t)m * g.Cols + col) = acc[i][j];
+      }
+    }
+    return;
+  }
+  T* __restrict__ Cg = (T*)g.C;
+  const bool stats = g.stats != nullptr, bstats = g.bstats != nullptr;
+  // output rows follow the GEMM rows when the output grid is the row grid
+  const bool dense = g.os == 1 && g.oph == 0 && g.opw == 0 && g.Hout == g.Hm && g.Wout == g.Wm;
+  float* Sh = (float*)smem;                        // [BN] shifts, then [NW][WTN] pairs of sums
+  float* St = Sh + BN;
+  float ssh[NC][VW], s1[NC][VW], s2[NC][VW];
+#pragma unroll
+  for (int p = 0; p < NC; ++p)
+#pragma unroll
+    for (int e = 0; e < VW; ++e) ssh[p][e] = s1[p][e] = s2[p][e] = 0.f;
+  if (stats) {
+    // the shift of a channel is its stored value in the tile's first row
+    if (wm == 0 && kx == 0 && l16 == 0) {
+#pragma unroll
+      for (int p = 0; p < NC; ++p)
+#pragma unroll
+        for (int e = 0; e < VW; ++e)
+          Sh[brow0 + q4 * VW + p * CST + e] = TT<T>::to_f(TT<T>::from_f(acc[0][p * TPC + e / 4][e % 4]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NC; ++p)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) ssh[p][e] = Sh[brow0 + q4 * VW + p * CST + e];
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + arow0 + 16 * i + l16;
+    if (m >= g.M || !mine(i)) continue;
+    uint32_t row = (uint32_t)m;
+    if (!dense) {
+      const int n = (int)g.fd_hw.div(m), rem = m - n * HWm;
+      const int ii = (int)g.fd_w.div(rem), jj = rem - ii * g.Wm;
+      row = (uint32_t)((n * g.Hout + ii * g.os + g.oph) * g.Wout + jj * g.os + g.opw);
+    }
+#pragma unroll
+    for (int p = 0; p < NC; ++p) {
+      const int col = col0 + p * CST;
+      if (col >= g.Cols) continue;
+      const uint32_t off = row * g.Cols + col;
+      float v[VW];
+#pragma unroll
+      for (int e = 0; e < VW; ++e) v[e] = acc[i][p * TPC + e / 4][e % 4];
+      if (g.mode == 1) {
+        float o[VW];
+        unpack<T>(*(const uint4*)(Cg + off), o);
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] += o[e];
+      } else if (g.mode == 2) {
+        float rr[VW];
+        unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
+        const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];    // mask byte of this 16-byte chunk
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] += (mk >> e) & 1u ? rr[e] : 0.f;
+      }
+      const uint4 pk = pack<T>(v);
+      *(uint4*)(Cg + off) = pk;
+      if (stats) {
+        float vr[VW];
+        unpack<T>(pk, vr);
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          const float d = vr[e] - ssh[p][e];
+          s1[p][e] += d;
+          s2[p][e] = __builtin_fmaf(d, d, s2[p][e]);
+        }
+      } else if (bstats) {
+        bwd_partial_add<T>(g, pk, off, col, s1[p], s2[p]);
+      }
+    }
+  }
+  if (!stats && !bstats) return;
+#pragma unroll
+  for (int p = 0; p < NC; ++p)
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+      const float r1 = row16_sum(s1[p][e]), r2 = row16_sum(s2[p][e]);
+      if (l16 == 0) *(float2*)(St + (wave * WTN + q4 * VW + p * CST + e) * 2) = make_float2(r1, r2);
+    }
+  __syncthreads();
+  const int rows = min(BM, g.M - m0);
+  for (int cl = tid; cl < BN; cl += NT) {
+    const int col = n0 + cl;
+    if (col >= g.Cols) continue;
+    const int wn_c = cl / WTN, cw = cl - wn_c * WTN;
+    float r1 = 0.f, r2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < WGM * KW; ++w) {
+      const float2 p = *(const float2*)(St + ((w * WGN + wn_c) * WTN + cw) * 2);
+      r1 += p.x;
+      r2 += p.y;
+    }
+    if (bstats) ((float2*)g.bstats)[(long)tm * g.Cols + col] = make_float2(r1, r2);
+    else ((float4*)g.stats)[(long)tm * g.Cols + col] = make_float4((float)rows, Sh[cl], r1, r2);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Wide halo conv: 3x3 stride-1 pad-1 convolutions of whole 128-byte channel
+// blocks to more than 64 columns, forward and data gradient, persistent.
+//
+// What bounds the gather tiles above on these layers is LDS and L2 traffic:
+// every tap loads its pixel rows again, so a 128x128 tile moves as many bytes
+// through LDS as its MFMAs read operands. Here a tile is up to 256 pixels
+// (TH whole image rows) x 128 columns; per channel block the input patch with
+// its halo is loaded once and all nine taps read it at a fixed pixel offset,
+// and only the weights of a tap (16 KB) stream through a ring of four. Rows
+// are counted over the whole batch, so a tile may span images: the patch has
+// one zero row between them (an image occupies H + 1 rows of it).
+//
+// A block walks tiles slot, slot + G, ...; the patch of the next channel block
+// or tile loads during the nine taps of the current one, in six parts, and the
+// output stores stay in flight during the next tile's taps. The grid is a
+// multiple of the column tiles, so that a block keeps its columns and the BN
+// statistics accumulate per lane over its tiles: one entry per row of waves.
+//
+// Operand order, weight rows, swizzles and the half-stage loop are those of
+// conv_gather_rp_kernel; so is the order of the K sum (channel blocks outer,
+// taps inner), and with it every result bit.
+// ---------------------------------------------------------------------------
+struct ConvHaloW {
+  ConvGather g;
+  FastDiv fd_h, fd_h1;   // division by H and H + 1
+  int TH, PW;            // output rows per tile, patch columns (W + 2)
+  int tiles_n, tiles;    // column tiles; tiles in all, column tile fastest
+};
+
+constexpr int HALOW_PROWS = 384;   // patch pixels per buffer
+constexpr int HALOW_BM = 256, HALOW_BN = 128, HALOW_WGM = 4, HALOW_NS = 4;
+
+template <typename T>
+__global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
+  constexpr int NW = 8, WGM = HALOW_WGM, WGN = 2, FM = 4, FN = 4, NS = HALOW_NS;
+  constexpr int VW = TT<T>::VW, KT = 128 / (int)sizeof(T), es = (int)sizeof(T);
+  constexpr int PB = HALOW_PROWS * 128, BB = HALOW_BN * 128;     // bytes of a patch buffer, of a weight stage
+  constexpr int PP = HALOW_PROWS / 8 / NW;                       // patch loads per wave (parts)
+  constexpr int UB = HALOW_BN / 8 / NW;                          // weight loads per wave and stage
+  constexpr int TPC = VW / 4, NC = FN / TPC, STORES = FM * NC;
+  constexpr int NF = FM + FN, NM = FM * FN * Mma<T>::SUB;
+  static_assert(2 * PB + NS * BB <= 163840 && PP <= 6 && NS == 4, "LDS, schedule");
+  __shared__ uint4 smem[(2 * PB + NS * BB) / 16];
+  const ConvGather& g = h.g;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int q4 = lane >> 4, l16 = lane & 15;
+  const uint32_t smem_lds = lds_addr(smem);
+  const int rowb = g.Cin * es, CB = g.Cin / KT, H = g.Hm, W = g.Wm;
+  const i32x4_t rsA = buffer_rsrc(g.A, (uint32_t)((long)g.N * H * W * rowb));
+  const i32x4_t rsB = buffer_rsrc(g.B, (uint32_t)((long)g.Cols * 9 * rowb));
+  const int G = gridDim.x;
+  const int slot = xcd_remap(blockIdx.x, G);
+  if (slot >= h.tiles) return;
+  const int tn = slot % h.tiles_n, n0 = tn * HALOW_BN;           // G is a multiple of tiles_n: the same for every tile
+  const int rows_all = g.N * H;
+
+  // ---- loads
+  int ppx[PP];                                     // patch row << 16 | patch column of this lane's loads
+#pragma unroll
+  for (int u = 0; u < PP; ++u) {
+    const int p = (wave + NW * u) * 8 + (lane >> 3), pr = p / h.PW;
+    ppx[u] = (pr << 16) | (p - pr * h.PW);
+  }
+  const int ca = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));         // key (patch pixel / 2) % 8
+  // part u of the patch of the tile at image n, row i0, channel block cb
+  auto load_patch = [&](int u, int n, int i0, int cb, uint32_t buf, bool live) {
+    const int v = i0 - 1 + (ppx[u] >> 16), c = (ppx[u] & 0xffff) - 1;    // row among the H + 1 rows of each image
+    const int dn = (int)h.fd_h1.div((uint32_t)(v < 0 ? 0 : v)), r = v - dn * (H + 1);
+    const bool ok = live && v >= 0 && r < H && n + dn < g.N && (unsigned)c < (unsigned)W;
+    const uint32_t off = (uint32_t)((((n + dn) * H + r) * W + c) * rowb + cb * 128 + ca * 16);
+    lds_dma16_buf(ok ? off : kOutOfRange, rsA, smem_lds + buf + (uint32_t)((wave + NW * u) * 1024));
+  };
+  uint32_t boff[UB];
+  {
+    const int c = VW == 8 ? (lane & 7) ^ (((lane >> 4) & 1) | ((wave & 3) << 1)) : ca;
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int col = n0 + (wave + NW * u) * 8 + (lane >> 3);
+      boff[u] = col < g.Cols ? (uint32_t)((long)col * 9 * rowb + c * 16) : kOutOfRange;
+    }
+  }
+  uint32_t bring = 2 * PB;                         // ring buffer of the weight stage issued next
+  auto load_w = [&](int u, int tap, int cb) {
+    const int th = tap / 3, tw = tap - 3 * th;
+    const uint32_t sb = (uint32_t)(((g.wkh0 + th * g.wkhs) * 3 + g.wkw0 + tw * g.wkws) * rowb + cb * 128);
+    lds_dma16_buf(boff[u] + sb, rsB, smem_lds + bring + (uint32_t)((wave + NW * u) * 1024));
+  };
+  auto next_ring = [&](uint32_t& r) { r = r == (uint32_t)(2 * PB + (NS - 1) * BB) ? (uint32_t)(2 * PB) : r + BB; };
+
+  // ---- operand fragments
+  const char* const sm = (const char*)smem;
+  const uint32_t lb = VW == 8 ? (uint32_t)((wn * 64 + 8 * (l16 >> 2) + (l16 & 3)) * 128 +
+                                           ((q4 ^ (((l16 >> 1) & 1) | ((l16 >> 2) << 1))) * 16))
+                              : (uint32_t)((wn * 64 + l16) * 128 + ((q4 ^ (l16 >> 1)) * 16));
+  int abase[FM];                                   // patch pixel of tap (0, 0) of this lane's pixels of the tile
+  auto tile_pixels = [&](int i0) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int q = wm * 64 + i * 16 + l16;
+      const int r = (int)g.fd_w.div((uint32_t)q), j = q - r * W;
+      // pixels past the tile's last row read patch pixels that exist
+      const int rr = r < h.TH ? r : 0;
+      abase[i] = (rr + (int)h.fd_h.div((uint32_t)(i0 + rr))) * h.PW + j;
+    }
+  };
+  uint4 a0[FM], b0[FN], a1[FM], b1[FN];
+  uint32_t cring = 2 * PB;                         // ring buffer of the weight stage in use
+  // (the patch width is made opaque per stage, so that the operand addresses
+  // are recomputed rather than held in registers for all nine taps)
+  int pw = h.PW;
+  auto read_frag = [&](int f, uint32_t pbuf, uint32_t wbuf, int tap, int x, uint4(&a)[FM], uint4(&b)[FN]) {
+    if (f < FN) {
+      const int row = VW == 8 ? (f >> 1) * 32 + (f & 1) * 4 : f * 16;
+      b[f] = *(const uint4*)(sm + ((wbuf + lb) ^ (uint32_t)(64 * x)) + row * 128);
+    } else {
+      const int pix = abase[f - FN] + (tap / 3) * pw + tap % 3;
+      a[f - FN] = *(const uint4*)(sm + pbuf + pix * 128 + (((4 * x + q4) ^ ((pix >> 1) & 7)) << 4));
+    }
+  };
+  floatx4_t acc[FM][FN];
+  auto half = [&](const uint4(&a)[FM], const uint4(&b)[FN], auto np, auto&& extra) {
+    constexpr int NP = decltype(np)::value;
+#pragma unroll
+    for (int m = 0; m < NM; m += 2) {
+#pragma unroll
+      for (int e = 0; e < NP; ++e)
+        if (e * NM / NP >= m && e * NM / NP < m + 2) extra(e);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = m; k < m + 2 && k < NM; ++k) {
+        const int tt = k / (FM * FN), r = k % (FM * FN);
+        Mma<T>::run(acc[r / FN][r % FN], b[r % FN], a[r / FN], tt);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // ---- epilogue state
+  T* __restrict__ Cg = (T*)g.C;
+  const __amdgpu_buffer_rsrc_t rsC =
+      __builtin_amdgcn_make_buffer_rsrc(g.C, 0, (uint32_t)((long)g.M * g.Cols * es), 0x00020000);
+  const bool stats = g.stats != nullptr, bstats = g.bstats != nullptr;
+  constexpr int CST = 16 * TPC;                    // channels between a lane's chunks
+  const int col0 = n0 + wn * 64 + q4 * VW;
+  float ssh[NC][VW], s1[NC][VW], s2[NC][VW];
+#pragma unroll
+  for (int p = 0; p < NC; ++p)
+#pragma unroll
+    for (int e = 0; e < VW; ++e) ssh[p][e] = s1[p][e] = s2[p][e] = 0.f;
+  bool have_shift = false;
+  int rows_acc = 0;
+
+  // ---- first patch and weight stages
+  int tile = slot;
+  int r0 = (tile / h.tiles_n) * h.TH, n = (int)h.fd_h.div((uint32_t)r0), i0 = r0 - n * H;
+#pragma unroll
+  for (int u = 0; u < PP; ++u) load_patch(u, n, i0, 0, 0u, true);
+#pragma unroll
+  for (int t = 0; t < NS; ++t) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u) load_w(u, t, 0);
+    next_ring(bring);
+  }
+  wait_vmcnt<(NS - 1) * UB>();
+  barrier_only();
+  tile_pixels(i0);
+#pragma unroll
+  for (int f = 0; f < NF; ++f) read_frag(f, 0u, cring, 0, 0, a0, b0);
+  uint32_t pbuf = 0;
+  bool stored = false;                             // the previous tile's stores were issued just before this chunk
+
+  while (true) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    const int ntile = tile + G, nr0 = (ntile / h.tiles_n) * h.TH;
+    const bool more = ntile < h.tiles;
+    const int nn = (int)h.fd_h.div((uint32_t)nr0), ni0 = nr0 - nn * H;
+    for (int cb = 0; cb < CB; ++cb) {
+      // the chunk (tile, channel block) after this one
+      const bool last = cb + 1 == CB, live = !last || more;
+      const int xn = last ? nn : n, xi0 = last ? ni0 : i0, xcb = last ? 0 : cb + 1;
+      const uint32_t xbuf = pbuf ^ (uint32_t)PB;
+      static_assert(PB == 0xC000, "");
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        asm volatile("" : "+s"(pw));
+        half(a0, b0, std::integral_constant<int, NF>{}, [&](int f) { read_frag(f, pbuf, cring, t, 1, a1, b1); });
+        // The weights of the next stage have landed, with every load issued
+        // before them (for t == 8 the next patch), and everybody has read this
+        // stage. Later than those weights (issued three stages ago) are the
+        // loads of the last two stages, PP patch parts in the first stages of
+        // a chunk among them, and for t <= 2 the stores of a tile that ended
+        // just before this chunk.
+        constexpr int NB2 = 2 * UB;
+        const int na = (t >= 1 && t - 1 < PP ? 1 : 0) + (t >= 2 && t - 2 < PP ? 1 : 0);
+        if (t <= 2 && stored) {
+          if (na == 0) wait_vmcnt<NB2 + STORES>();
+          else if (na == 1) wait_vmcnt<NB2 + 1 + STORES>();
+          else wait_vmcnt<NB2 + 2 + STORES>();
+        } else {
+          if (na == 0) wait_vmcnt<NB2>();
+          else if (na == 1) wait_vmcnt<NB2 + 1>();
+          else wait_vmcnt<NB2 + 2>();
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        barrier_only();
+        next_ring(cring);
+        if (t == 8 && last) tile_pixels(xi0);
+        const int wt = t + NS < 9 ? t + NS : t + NS - 9, wcb = t + NS < 9 ? cb : xcb;
+        // loads first among the extras: the patch part, the weights of stage s + 4
+        half(a1, b1, std::integral_constant<int, NF + 1 + UB>{}, [&](int e) {
+          if (e < NF) {
+            read_frag(e, t == 8 ? xbuf : pbuf, cring, t == 8 ? 0 : t + 1, 0, a0, b0);
+          } else if (e == NF) {
+            if (t < PP) load_patch(t, xn, xi0, xcb, xbuf, live);
+          } else {
+            load_w(e - NF - 1, wt, wcb);
+          }
+        });
+        next_ring(bring);
+      }
+      stored = false;
+      pbuf = xbuf;
+    }
+
+    // ---- epilogue straight from registers; stores past the tile are dropped
+    // by the buffer's range check, so every wave issues STORES of them
+    const int tr = min(h.TH, rows_all - r0), npx = tr * W;
+    const uint32_t m0 = (uint32_t)r0 * W;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int q = wm * 64 + i * 16 + l16;
+      const bool okq = q < npx;
+#pragma unroll
+      for (int p = 0; p < NC; ++p) {
+        const int col = col0 + p * CST;
+        const bool ok = okq && col < g.Cols;
+        const uint32_t off = (m0 + (uint32_t)(okq ? q : 0)) * g.Cols + (uint32_t)(col < g.Cols ? col : 0);
+        float v[VW];
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] = acc[i][p * TPC + e / 4][e % 4];
+        if (g.mode == 1) {
+          float o[VW];
+          unpack<T>(*(const uint4*)(Cg + off), o);
+#pragma unroll
+          for (int e = 0; e < VW; ++e) v[e] += o[e];
+        } else if (g.mode == 2) {
+          float rr[VW];
+          unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
+          const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];    // mask byte of this 16-byte chunk
+#pragma unroll
+          for (int e = 0; e < VW; ++e) v[e] += (mk >> e) & 1u ? rr[e] : 0.f;
+        }
+        const uint4 pk = pack<T>(v);
+        typedef int i32x4v_t __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4v_t, pk), rsC, ok ? off * es : kOutOfRange, 0, 0);
+        if (stats) {
+          float vr[VW];
+          unpack<T>(pk, vr);
+          if (!have_shift && i == 0) {
+            // the wave's first pixel (of its first tile) is its statistics shift
+#pragma unroll
+            for (int e = 0; e < VW; ++e) ssh[p][e] = __shfl(vr[e], lane & 48, 64);
+          }
+#pragma unroll
+          for (int e = 0; e < VW; ++e) {
+            const float d = okq ? vr[e] - ssh[p][e] : 0.f;
+            s1[p][e] += d;
+            s2[p][e] = __builtin_fmaf(d, d, s2[p][e]);
+          }
+        } else if (bstats) {
+          if (ok) bwd_partial_add<T>(g, pk, off, col, s1[p], s2[p]);
+        }
+      }
+    }
+    if (wm * 64 < npx) {
+      have_shift = true;
+      rows_acc += min(64, npx - wm * 64);
+    }
+    if (!more) break;
+    stored = true;
+    tile = ntile;
+    r0 = nr0;
+    n = nn;
+    i0 = ni0;
+  }
+  if (stats || bstats) {
+    // one entry per row of waves: its pixels over all of the block's tiles
+    const long entry = (long)(slot / h.tiles_n) * WGM + wm;
+#pragma unroll
+    for (int p = 0; p < NC; ++p)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        const float x1 = row16_sum(s1[p][e]), x2 = row16_sum(s2[p][e]);
+        const int col = col0 + p * CST + e;
+        if (l16 == 0 && col < g.Cols) {
+          if (bstats) ((float2*)g.bstats)[entry * g.Cols + col] = make_float2(x1, x2);
+          else ((float4*)g.stats)[entry * g.Cols + col] = make_float4((float)rows_acc, ssh[p][e], x1, x2);
+        }
+      }
+  }
+  wait_vmcnt<0>();
 }
 
 // ---------------------------------------------------------------------------
@@ -751,7 +1376,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, gather_occupancy(BM, BN, WGM * WGN,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave_u / WGN, wn = wave_u % WGN;
-  const int c = (lane & 7) ^ (((wave_u & 1) << 2) | (lane >> 4));   // see gather_impl
+  const int c = (lane & 7) ^ (((wave_u & 1) << 2) | (lane >> 4));   // see conv_gather2_kernel
   const uint32_t smem_lds = lds_addr(smem);
   const int G = gridDim.x;
   const int slot = xcd_remap(blockIdx.x, G);
@@ -2211,36 +2836,48 @@ bool gather_uniform(const ConvGather& g, int kt) {
          (long)g.Cols * g.KHW * g.Cin * es < (1l << 31);
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, bool RP>
-int launch_gather2(const ConvGather& g0, hipStream_t s) {
-  ConvGather g = g0;
+// The launch's divisors, zero page and split scratch, checked; 0 or an error.
+int gather_prepare(ConvGather& g) {
   g.fd_hw = FastDiv((uint32_t)(g.Hm * g.Wm));
   g.fd_w = FastDiv((uint32_t)g.Wm);
   if ((long)g.N * g.Hout * g.Wout * g.Cols >= (1l << 31)) return -1;  // 32-bit output offsets
   g.zero = zero_page();
   if (!g.zero) return -4;
   if (g.ksplit > 1 && (!g.part || ((uintptr_t)g.part & 15))) return -1;
-  const int ks = g.ksplit > 1 ? g.ksplit : 1;
-  const int tiles = ceil_div(g.M, BM) * ceil_div(g.Cols, BN);
-  const int kt = 128 / (int)sizeof(T);
-  const int nt = 64 * WGM * WGN;
-  const dim3 grid(tiles * ks);
-  if constexpr (RP) {
-    if (gather_uniform(g, kt))
-      hipLaunchKernelGGL((conv_gather_rp_kernel<T, BM, BN, WGM, WGN, STAGES, true>), grid, dim3(nt), 0, s, g);
-    else
-      hipLaunchKernelGGL((conv_gather_rp_kernel<T, BM, BN, WGM, WGN, STAGES, false>), grid, dim3(nt), 0, s, g);
-  } else {
-    if (gather_uniform(g, kt))
-      hipLaunchKernelGGL((conv_gather2_kernel<T, BM, BN, WGM, WGN, STAGES, true>), grid, dim3(nt), 0, s, g);
-    else
-      hipLaunchKernelGGL((conv_gather2_kernel<T, BM, BN, WGM, WGN, STAGES, false>), grid, dim3(nt), 0, s, g);
-  }
-  if (ks > 1) {
+  return 0;
+}
+
+template <typename T>
+int gather_finish(const ConvGather& g, hipStream_t s) {
+  if (g.ksplit > 1) {
     const int rb = ceil_div(g.M, SK_ROWS) * ceil_div(g.Cols, SK_COLS);
     hipLaunchKernelGGL(gather_splitk_reduce_kernel<T>, dim3(rb), dim3(256), 0, s, g);
   }
   return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int STAGES>
+int launch_gather2(const ConvGather& g0, hipStream_t s) {
+  ConvGather g = g0;
+  if (const int r = gather_prepare(g)) return r;
+  const int ks = g.ksplit > 1 ? g.ksplit : 1;
+  const dim3 grid(ceil_div(g.M, BM) * ceil_div(g.Cols, BN) * ks), block(64 * WGM * WGN);
+  if (gather_uniform(g, 128 / (int)sizeof(T)))
+    hipLaunchKernelGGL((conv_gather2_kernel<T, BM, BN, WGM, WGN, STAGES, true>), grid, block, 0, s, g);
+  else
+    hipLaunchKernelGGL((conv_gather2_kernel<T, BM, BN, WGM, WGN, STAGES, false>), grid, block, 0, s, g);
+  return gather_finish<T>(g, s);
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int KW, int STAGES>
+int launch_gather_rp(const ConvGather& g0, hipStream_t s) {
+  ConvGather g = g0;
+  if (const int r = gather_prepare(g)) return r;
+  if (!gather_uniform(g, 128 / (int)sizeof(T))) return -1;
+  const int ks = g.ksplit > 1 ? g.ksplit : 1;
+  const dim3 grid(ceil_div(g.M, BM) * ceil_div(g.Cols, BN) * ks), block(64 * WGM * WGN * KW);
+  hipLaunchKernelGGL((conv_gather_rp_kernel<T, BM, BN, WGM, WGN, KW, STAGES>), grid, block, 0, s, g);
+  return gather_finish<T>(g, s);
 }
 
 int cu_count() {
@@ -2379,37 +3016,97 @@ int launch_halo(const ConvGather& g0, int th, hipStream_t s) {
 }
 
 
-// Kernel configurations: id -> (BM, BN, waves along M, waves along N, stages,
-// kind: 0 plain loop, 1 register-prefetched loop, 2 persistent).
-#define RN18_GATHER_CONFIGS(X)                                                                                  \
-  X(1, 64, 32, 2, 2, 3, 0) X(2, 64, 64, 2, 2, 3, 0) X(3, 128, 64, 2, 2, 3, 0) X(4, 128, 128, 2, 2, 3, 0)        \
-  X(5, 256, 128, 4, 2, 3, 0) X(6, 256, 128, 2, 2, 3, 0) X(7, 256, 64, 4, 2, 3, 0) X(8, 128, 128, 2, 4, 3, 0)    \
-  X(9, 256, 64, 4, 1, 3, 0) X(10, 128, 128, 2, 2, 2, 0) X(11, 256, 128, 4, 2, 2, 0) X(12, 128, 64, 2, 2, 4, 0)  \
-  X(13, 128, 64, 2, 2, 2, 0) X(14, 64, 64, 2, 2, 2, 0) X(15, 256, 64, 4, 2, 2, 0) X(16, 128, 128, 2, 4, 2, 0)   \
-  X(17, 256, 128, 2, 2, 2, 0) X(18, 512, 64, 4, 1, 2, 0) X(19, 256, 128, 2, 2, 3, 0) X(20, 128, 128, 2, 2, 4, 0) \
-  X(21, 256, 64, 4, 1, 2, 0) X(22, 256, 64, 2, 2, 2, 0) X(23, 128, 128, 2, 2, 2, 1) X(24, 256, 128, 4, 2, 2, 1) \
-  X(25, 256, 64, 4, 1, 2, 1) X(26, 128, 128, 2, 4, 2, 1) X(27, 256, 64, 4, 2, 2, 1) X(28, 256, 128, 4, 2, 3, 1)  \
-  X(29, 128, 128, 2, 2, 3, 1) X(30, 512, 64, 8, 1, 2, 1) X(31, 128, 256, 2, 4, 2, 1) X(32, 128, 64, 2, 2, 2, 1)  \
-  X(33, 64, 64, 2, 2, 2, 1) X(34, 256, 64, 4, 1, 3, 1) X(35, 256, 64, 4, 2, 2, 2) X(36, 128, 128, 2, 4, 2, 2)   \
-  X(37, 128, 64, 2, 2, 2, 2) X(38, 64, 64, 2, 2, 2, 2) X(39, 256, 128, 4, 2, 2, 2) X(40, 128, 128, 2, 2, 2, 2)  \
-  X(41, 128, 256, 2, 4, 2, 2) X(42, 128, 128, 2, 4, 3, 2) X(43, 256, 64, 4, 2, 3, 2) X(44, 128, 64, 2, 2, 3, 2)
+// Image rows per tile of the wide halo kernel for a launch, or 0 when the
+// launch is not one it handles (16-bit, a 3x3 stride-1 pad-1 walk of whole
+// 128-byte channel blocks, more than 64 columns, output grid = row grid).
+int halow_rows(int prec, const ConvGather& g) {
+  if (prec == PREC_F32 || g.Cin % 64 || g.Cols <= 64 || g.nth != 3 || g.ntw != 3 || g.KHW != 9 || g.KW != 3 ||
+      g.K != 9 * g.Cin || g.K2)
+    return 0;
+  if (g.is != 1 || g.ip != 1 || g.os != 1 || g.oph != 0 || g.opw != 0 || g.dh0 != 0 || g.dw0 != 0 || g.dhs != 1 ||
+      g.dws != 1)
+    return 0;
+  if (g.Hin != g.Hm || g.Win != g.Wm || g.Hout != g.Hm || g.Wout != g.Wm || g.Hm < 1 || g.Wm < 1) return 0;
+  if ((long)g.N * g.Hin * g.Win * g.Cin * 2 >= (1l << 31) || (long)g.M * g.Cols * 2 >= (1l << 31) ||
+      (long)g.Cols * 9 * g.Cin * 2 >= (1l << 31) || (long)g.N * (g.Hm + 1) >= (1l << 30))
+    return 0;
+  // as many whole rows as fit 256 pixels and the patch, with one zero row
+  // between the images that a tile touches; at least 192 pixels keep the MFMA
+  // tiles filled (and the statistics entries, four per block, at most one per
+  // 32 GEMM rows)
+  const int H = g.Hm, W = g.Wm;
+  int th = HALOW_BM / W;
+  while (th > 0) {
+    const int cross = th % H == 0 ? th / H - 1 : (th - 1 + H - 1) / H;
+    if ((th + 2 + cross) * (W + 2) <= HALOW_PROWS) break;
+    --th;
+  }
+  if (th < 1 || th * W < 192 || (long)th * W > g.M) return 0;
+  return th;
+}
+int halow_grid(const ConvGather& g, int th) {
+  const int tiles_n = ceil_div(g.Cols, HALOW_BN), tiles = ceil_div((long)g.N * g.Hm, th) * tiles_n;
+  const int most = cu_count() / tiles_n * tiles_n;   // a block keeps its column tile
+  return tiles < most ? tiles : most;
+}
+
+template <typename T>
+int launch_halow(const ConvGather& g0, int th, hipStream_t s) {
+  ConvHaloW h{};
+  h.g = g0;
+  h.g.fd_hw = FastDiv((uint32_t)(g0.Hm * g0.Wm));
+  h.g.fd_w = FastDiv((uint32_t)g0.Wm);
+  h.fd_h = FastDiv((uint32_t)g0.Hm);
+  h.fd_h1 = FastDiv((uint32_t)(g0.Hm + 1));
+  h.TH = th;
+  h.PW = g0.Wm + 2;
+  h.tiles_n = ceil_div(g0.Cols, HALOW_BN);
+  h.tiles = ceil_div((long)g0.N * g0.Hm, th) * h.tiles_n;
+  const int grid = halow_grid(g0, th);
+  if (grid < 1) return -4;
+  hipLaunchKernelGGL(conv_halow_kernel<T>, dim3(grid), dim3(512), 0, s, h);
+  return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+// Kernel configurations: id -> (BM, BN, waves along M, waves along N, waves
+// along K, stages, kind: 0 plain loop, 1 half-stage pipelined, 2 persistent).
+#define RN18_GATHER_CONFIGS(X)                                                                                     \
+  X(1, 64, 32, 2, 2, 1, 3, 0) X(2, 64, 64, 2, 2, 1, 3, 0) X(3, 128, 64, 2, 2, 1, 2, 1)                             \
+  X(4, 128, 128, 2, 4, 1, 2, 1) X(5, 256, 128, 4, 2, 1, 3, 1) X(6, 256, 128, 2, 2, 2, 3, 1)                        \
+  X(7, 256, 64, 4, 2, 1, 3, 1) X(8, 128, 128, 2, 4, 1, 4, 1) X(9, 64, 64, 2, 2, 1, 2, 1)                           \
+  X(10, 64, 64, 2, 2, 1, 4, 1) X(11, 224, 128, 2, 2, 2, 3, 1) X(12, 448, 128, 4, 2, 1, 2, 1)                       \
+  X(13, 128, 64, 2, 2, 1, 2, 0) X(14, 64, 64, 2, 2, 1, 2, 0) X(15, 256, 64, 4, 2, 1, 2, 0)                         \
+  X(16, 128, 128, 2, 4, 1, 2, 0) X(17, 224, 256, 2, 4, 1, 2, 1) X(18, 512, 128, 4, 2, 1, 2, 1)                     \
+  X(19, 256, 256, 2, 4, 1, 2, 1) X(20, 64, 128, 1, 2, 2, 2, 1) X(21, 128, 128, 2, 2, 2, 4, 1)                      \
+  X(22, 256, 64, 4, 2, 1, 2, 1)                                                                                    \
+  X(35, 256, 64, 4, 2, 1, 2, 2) X(36, 128, 128, 2, 4, 1, 2, 2) X(37, 128, 64, 2, 2, 1, 2, 2)                       \
+  X(38, 64, 64, 2, 2, 1, 2, 2) X(39, 256, 128, 4, 2, 1, 2, 2) X(40, 128, 128, 2, 2, 1, 2, 2)                       \
+  X(41, 128, 256, 2, 4, 1, 2, 2) X(42, 128, 128, 2, 4, 1, 3, 2) X(43, 256, 64, 4, 2, 1, 3, 2)                      \
+  X(44, 128, 64, 2, 2, 1, 3, 2)
 constexpr int kGatherCfgs = 44;
-constexpr int kGatherHalo = 45;  // the halo kernel where it applies, else the automatic choice
+constexpr int kGatherHaloW = 34;  // the wide halo kernel where it applies (ids 23..33 name the kernels of 3..13)
+constexpr int kGatherHalo = 45;   // the halo kernels where they apply, else the automatic choice
 int g_gather_override = 0;
 
-struct GatherCfg { int bm, bn, wgm, wgn, stages, kind; };
-constexpr GatherCfg kGather[kGatherCfgs + 1] = {
-    {0, 0, 0, 0, 0, 0},
-#define RN18_X(id, bm, bn, wgm, wgn, st, kind) {bm, bn, wgm, wgn, st, kind},
+struct GatherCfg { int id, bm, bn, wgm, wgn, kw, stages, kind; };
+constexpr GatherCfg kGatherList[] = {
+#define RN18_X(id, bm, bn, wgm, wgn, kw, st, kind) {id, bm, bn, wgm, wgn, kw, st, kind},
     RN18_GATHER_CONFIGS(RN18_X)
 #undef RN18_X
 };
+const GatherCfg& gather_entry(int id) {
+  for (const GatherCfg& c : kGatherList)
+    if (c.id == id) return c;
+  return kGatherList[0];
+}
 
-// Choice measured on MI355X over the ResNet-18 shapes (bf16 224x224 batch 256,
-// fp32 32x32 batch 128): two-stage rings with two or more blocks per CU beat
-// deeper rings with one block; 8-wave blocks for the large tiles.
-int gather_cfg(const ConvGather& g) {
-  if (g_gather_override && g_gather_override != kGatherHalo) return g_gather_override;
+// Accumulator registers per lane: the fp32 instances (four MFMAs per operand
+// pair) are built for at most 64.
+constexpr int gather_acc(int bm, int bn, int waves) { return bm * bn / (waves * 64); }
+
+// Plain-loop configuration of a launch: the rows are not uniform, or a small
+// column count.
+int gather_plain(const ConvGather& g) {
   if (g.Cols <= 32) return 1;
   if (g.Cols <= 64) return g.M >= 131072 ? 15 : g.M >= 65536 ? 13 : 14;
   return (long)ceil_div(g.M, 128) * ceil_div(g.Cols, 128) >= 256 ? 16 : 14;
@@ -2429,14 +3126,132 @@ constexpr long kSplitBlocks = 640;
 constexpr long kSplitMaxTiles = 255;
 constexpr int kSplitMinStages = 8;
 
+int gather_auto(int prec, const ConvGather& g);
+
+// Configuration of a launch: the forced one where it can run, else the
+// automatic choice.
+int gather_cfg(int prec, const ConvGather& g) {
+  int id = g_gather_override;
+  if (id == 0 || id == kGatherHalo) return gather_auto(prec, g);
+  if (id == kGatherHaloW) return halow_rows(prec, g) > 0 ? kGatherHaloW : gather_auto(prec, g);
+  if (id > 22 && id < kGatherHaloW) id -= 20;
+  const GatherCfg& c = gather_entry(id);
+  if (c.kind == 1) {
+    if (!gather_uniform(g, 128 / prec_bytes(prec))) return gather_plain(g);
+    if (prec == PREC_F32 && gather_acc(c.bm, c.bn, c.wgm * c.wgn * c.kw) > 64) return 4;
+  }
+  return id;
+}
+
+// Automatic choice among the uniform-row kernels for more than 64 columns, by
+// estimated time in microseconds. In 16-bit types a round of tiles with b
+// resident blocks per CU costs f + b - 1 + S c[b], S the stages of K, and h
+// more where the epilogue reads operands (a residual, BN backward partials).
+// The constants are fitted (within about 10%) to the launches of training steps
+// on MI355X, batch 64 to 256 at 128 to 224 pixels, each configuration forced
+// in turn: weights come cold from the Infinity Cache there, so deep rings win
+// on small grids (us, K 2304: 4096 x 256: 10 19, 14 32; 9600 x 256: 8 26, 14
+// 33; K 4608: 1024 x 512: 10 in two K ranges 24, five ranges of 14 28). On
+// large grids the wide halo kernel has the cheapest stages, the 224x256 and
+// 448x128 tiles read the fewest LDS bytes per MFMA but pay f per tile, and
+// two resident 128x128 blocks hide an epilogue with operands best (200704 x
+// 128, K 1152: 34 70, 16 81; with a residual 16 87, 34 93; 50176 x 256, K
+// 2304: 12 60, 17 62, 16 75; 12544 x 512, K 4608: 11 61, 34 62, 16 71).
+// In fp32 the MFMAs bound every tile alike: the choice spreads the tiles most
+// evenly over the CUs, weighted by the measured share of the MFMA rate (f: with
+// one resident block, c[0]: with more). 36864 x 128, K 1152: 9 99 us, 16 147.
+struct GatherCost { int id, bmax; float f, h, c[5]; };
+constexpr GatherCost kCost16[] = {
+    {14, 5, 1.f, 1.3f, {.62f, .66f, .68f, .72f, .88f}}, {10, 2, 1.5f, 1.9f, {.28f, .32f}},
+    {20, 3, 5.f, 5.f, {.50f, .58f, .69f}},              {8, 1, 3.f, 4.3f, {.46f}},
+    {16, 2, 6.f, 4.f, {.50f, .76f}},                    {11, 1, 9.5f, 8.5f, {.60f}},
+    {5, 1, 7.5f, 9.f, {.71f}},                          {6, 1, 10.f, 9.f, {.64f}},
+    {12, 1, 15.5f, 10.f, {1.05f}},                      {18, 1, 16.5f, 10.f, {1.16f}},
+    {17, 1, 14.f, 6.f, {1.14f}},                        {19, 1, 16.f, 6.f, {1.16f}},
+    {kGatherHaloW, 1, 3.5f, 9.f, {.75f}},
+};
+constexpr GatherCost kCost32[] = {
+    {14, 5, 1.54f, 0.f, {1.36f}}, {9, 5, 1.6f, 0.f, {1.27f}}, {10, 2, 1.6f, 0.f, {1.30f}},
+    {20, 3, 1.32f, 0.f, {1.20f}}, {4, 2, 1.28f, 0.f, {1.28f}},
+};
+
+float gather_est(int prec, const GatherCost& e, long tiles, int S, long cus, bool operands) {
+  if (prec == PREC_F32) {
+    const GatherCfg& c = gather_entry(e.id);
+    const long per = (tiles + cus - 1) / cus;
+    return 7.f + (float)per * S * 0.427f * (c.bm * c.bn / 4096.f) * (per > 1 ? e.c[0] : e.f);
+  }
+  const long slots = cus * e.bmax, full = tiles / slots, rest = tiles - full * slots;
+  auto round = [&](long b) { return e.f + (operands ? e.h : 0.f) + (float)(b - 1) + S * e.c[b - 1]; };
+  return 7.f + (float)full * round(e.bmax) + (rest > 0 ? round((rest + cus - 1) / cus) : 0.f);
+}
+
+// The choice for a launch: its configuration, and the split count of K when
+// the caller gave scratch for it (see gather_split). A split launch pays its
+// reduction: a launch and the fp32 partials written and read.
+int gather_best(int prec, const ConvGather& g, int* split) {
+  const int S = ceil_div(g.K, 128 / prec_bytes(prec));
+  const bool can_split = g.ws && ((uintptr_t)g.ws & 15) == 0 && g_gather_split != 1 && !g.K2;
+  const long cus = cu_count() > 0 ? cu_count() : 256;
+  const bool operands = g.mode != 0 || g.bstats;
+  int best = 0;
+  float tb = 0.f;
+  *split = 1;
+  auto consider = [&](const GatherCost& e) {
+    long tiles;
+    if (e.id == kGatherHaloW) {
+      const int th = halow_rows(prec, g);
+      if (th < 1) return;
+      tiles = (long)ceil_div((long)g.N * g.Hm, th) * ceil_div(g.Cols, HALOW_BN);
+    } else {
+      const GatherCfg& c = gather_entry(e.id);
+      tiles = (long)ceil_div(g.M, c.bm) * ceil_div(g.Cols, c.bn);
+    }
+    const float t = gather_est(prec, e, tiles, S, cus, operands);
+    if (!best || t < tb) { best = e.id; tb = t; *split = 1; }
+    if (!can_split || e.id == kGatherHaloW || tiles > kSplitMaxTiles) return;
+    const double mn = (double)g.M * g.Cols * 4;
+    for (int k = 2; k <= 8 && S / k >= kSplitMinStages; ++k) {
+      if (mn * k > (double)g.ws_bytes) break;
+      const float ts = gather_est(prec, e, tiles * k, ceil_div(S, k), cus, operands) + 4.f + (float)(mn * (k + 1) / 3.5e6);
+      if (ts < tb) { best = e.id; tb = ts; *split = k; }
+    }
+  };
+  if (prec == PREC_F32)
+    for (const GatherCost& e : kCost32) consider(e);
+  else
+    for (const GatherCost& e : kCost16) consider(e);
+  return best;
+}
+
+// At most four stages of K: the plain loop (see kCost16).
+bool gather_short(int prec, const ConvGather& g) { return g.K <= 4 * (128 / prec_bytes(prec)); }
+
+int gather_auto(int prec, const ConvGather& g) {
+  if (g.Cols <= 32 || !gather_uniform(g, 128 / prec_bytes(prec))) return gather_plain(g);
+  if (g.Cols <= 64) {
+    // 64 columns: 256x64 tiles where they fill the chip, else 64x64 (fp32,
+    // 147456 rows, K 576: 64x64 95 us, 256x64 121 us; 131072 rows: 83 and 81)
+    const long t256 = ceil_div(g.M, 256);
+    if (prec == PREC_F32) return t256 % 512 == 0 || t256 >= 2048 ? 22 : 9;
+    return g.M >= 131072 ? 22 : g.M >= 65536 ? 3 : 9;
+  }
+  if (gather_short(prec, g)) return gather_plain(g);
+  int split;
+  return gather_best(prec, g, &split);
+}
+
 int gather_split_want(int prec, const ConvGather& g, int id) {
-  if (id < 1 || id > kGatherCfgs || kGather[id].kind == 2 || g.K2 || g_gather_split == 1) return 1;
+  if (id == kGatherHaloW || gather_entry(id).kind == 2 || g.K2 || g_gather_split == 1) return 1;
   const int S = ceil_div(g.K, 128 / prec_bytes(prec));
   int k;
   if (g_gather_split > 1) {
     k = g_gather_split;
+  } else if (g.Cols > 64 && !gather_short(prec, g) && (g_gather_override == 0 || g_gather_override == kGatherHalo) &&
+             gather_uniform(g, 128 / prec_bytes(prec))) {
+    gather_best(prec, g, &k);
   } else {
-    const long tiles = (long)ceil_div(g.M, kGather[id].bm) * ceil_div(g.Cols, kGather[id].bn);
+    const long tiles = (long)ceil_div(g.M, gather_entry(id).bm) * ceil_div(g.Cols, gather_entry(id).bn);
     if (tiles > kSplitMaxTiles) return 1;
     k = (int)((kSplitBlocks + tiles / 2) / tiles);
     if (k > S / kSplitMinStages) k = S / kSplitMinStages;
@@ -2463,11 +3278,15 @@ bool use_halo16(int prec, const ConvGather& g) {
   return (g_gather_override == 0 || g_gather_override == kGatherHalo) && halo16_rows(prec, g) > 0;
 }
 
+int gather_id_tile(int id) {
+  if (id == kGatherHaloW) return HALOW_BM * 1000 + HALOW_BN;
+  return gather_entry(id).bm * 1000 + gather_entry(id).bn;
+}
+
 int gather_tile(int prec, const ConvGather& g) {
   if (use_halo(prec, g)) return HALO_BM * 1000 + 64;
   if (use_halo16(prec, g)) return HALO16_BM * 1000 + 64;
-  const int id = gather_cfg(g);
-  return id >= 1 && id <= kGatherCfgs ? kGather[id].bm * 1000 + kGather[id].bn : 0;
+  return gather_id_tile(gather_cfg(prec, g));
 }
 
 // The sub-problems of one launch share the configuration chosen for the
@@ -2483,8 +3302,8 @@ bool gather_has_seg2(const ConvGather* g, int np) {
     if (g[i].K2) return true;
   return false;
 }
-int gather_cfg_multi(const ConvGather* g, int np) {
-  if (!gather_has_seg2(g, np) && (g_gather_override || np < 2)) return gather_cfg(g[0]);
+int gather_cfg_multi(int prec, const ConvGather* g, int np) {
+  if (!gather_has_seg2(g, np) && (g_gather_override || np < 2)) return gather_cfg(prec, g[0]);
   return g[0].Cols <= 64 ? 35 : g[0].Cols <= 128 ? 36 : 37;
 }
 
@@ -2498,21 +3317,31 @@ int gather_dispatch(const ConvGather* g, int np, hipStream_t s) {
     if (!seg2 && np == 1 && use_halo(prec, g[0])) return launch_halo<T>(g[0], halo_rows(prec, g[0]), s);
     if (!seg2 && np == 1 && use_halo16(prec, g[0])) return launch_halo16<T>(g[0], halo16_rows(prec, g[0]), s);
   }
-  switch (gather_cfg_multi(g, np)) {
-#define RN18_X(id, bm, bn, wgm, wgn, st, kind)                                               \
-  case id:                                                                                 \
-    if constexpr (kind == 2) {                                                             \
-      const int r = launch_gather_ps<T, bm, bn, wgm, wgn, st>(g, np, s);                   \
-      if (r != -1 || seg2) return r;                                                       \
-    }                                                                                      \
-    for (int i = 0; i < np; ++i) {                                                         \
-      if (g[i].M <= 0) continue;                                                           \
-      ConvGather gi = g[i];                                                                \
-      gi.ksplit = gather_split(prec, gi, id);                                              \
-      gi.part = (float*)gi.ws;                                                             \
-      const int r = launch_gather2<T, bm, bn, wgm, wgn, st, kind == 1>(gi, s);             \
-      if (r) return r;                                                                     \
-    }                                                                                      \
+  const int cfg = gather_cfg_multi(prec, g, np);
+  if (cfg == kGatherHaloW) {
+    if constexpr (sizeof(T) == 2) {
+      if (np == 1) return launch_halow<T>(g[0], halow_rows(prec, g[0]), s);
+    }
+    return -1;
+  }
+  switch (cfg) {
+#define RN18_X(id, bm, bn, wgm, wgn, kw, st, kind)                                                         \
+  case id:                                                                                                 \
+    if constexpr (kind == 2) {                                                                             \
+      const int r = launch_gather_ps<T, bm, bn, wgm, wgn, st>(g, np, s);                                   \
+      if (r != -1 || seg2) return r;                                                                       \
+    }                                                                                                      \
+    for (int i = 0; i < np; ++i) {                                                                         \
+      if (g[i].M <= 0) continue;                                                                           \
+      ConvGather gi = g[i];                                                                                \
+      gi.ksplit = gather_split(prec, gi, id);                                                              \
+      gi.part = (float*)gi.ws;                                                                             \
+      int r = -1;                                                                                          \
+      if constexpr (kind != 1) r = launch_gather2<T, bm, bn, wgm, wgn, st>(gi, s);                         \
+      else if constexpr (sizeof(T) == 2 || gather_acc(bm, bn, wgm * wgn * kw) <= 64)                       \
+        r = launch_gather_rp<T, bm, bn, wgm, wgn, kw, st>(gi, s);                                          \
+      if (r) return r;                                                                                     \
+    }                                                                                                      \
     return 0;
     RN18_GATHER_CONFIGS(RN18_X)
 #undef RN18_X
@@ -2647,26 +3476,28 @@ const char* conv_gather_kernel_name(int prec, const ConvGather& g) {
     snprintf(buf, sizeof buf, "conv_halo16_kernel<%s, %s>", type_name(prec), g.stats ? "true" : "false");
     return intern_name(buf);
   }
-  return gather_kernel_name(prec, g, gather_cfg(g));
+  return gather_kernel_name(prec, g, gather_cfg(prec, g));
 }
 
 const char* conv_gather_kernel_name_multi(int prec, const ConvGather* g, int np) {
   if (np == 1 && !g[0].K2) return conv_gather_kernel_name(prec, g[0]);
-  return gather_kernel_name(prec, g[0], gather_cfg_multi(g, np));
+  return gather_kernel_name(prec, g[0], gather_cfg_multi(prec, g, np));
 }
 
 const char* gather_kernel_name(int prec, const ConvGather& g, int id) {
-  if (id < 1 || id > kGatherCfgs) return "conv_gather2_kernel";
-  const GatherCfg& c = kGather[id];
-  const int kt = 128 / prec_bytes(prec);
+  if (id == kGatherHaloW) return kernel_instance_name("conv_halow_kernel", prec);
+  const GatherCfg& c = gather_entry(id);
+  const bool uni = gather_uniform(g, 128 / prec_bytes(prec));
   char buf[128];
-  if (c.kind == 2 && gather_uniform(g, kt))
+  if (c.kind == 2 && uni)
     snprintf(buf, sizeof buf, "conv_gather_ps_kernel<%s, %d, %d, %d, %d, %d>", type_name(prec), c.bm, c.bn, c.wgm,
              c.wgn, c.stages);
+  else if (c.kind == 1)
+    snprintf(buf, sizeof buf, "conv_gather_rp_kernel<%s, %d, %d, %d, %d, %d, %d>", type_name(prec), c.bm, c.bn, c.wgm,
+             c.wgn, c.kw, c.stages);
   else
-    snprintf(buf, sizeof buf, "%s<%s, %d, %d, %d, %d, %d, %s>",
-             c.kind == 1 ? "conv_gather_rp_kernel" : "conv_gather2_kernel", type_name(prec), c.bm, c.bn, c.wgm, c.wgn,
-             c.stages, gather_uniform(g, kt) ? "true" : "false");
+    snprintf(buf, sizeof buf, "conv_gather2_kernel<%s, %d, %d, %d, %d, %d, %s>", type_name(prec), c.bm, c.bn, c.wgm,
+             c.wgn, c.stages, uni ? "true" : "false");
   return intern_name(buf);
 }
 
@@ -2695,8 +3526,17 @@ int conv_gather_tile(int prec, const ConvGather& g) { return gather_tile(prec, g
 
 int conv_gather_tile_multi(int prec, const ConvGather* g, int np) {
   if (np == 1 && !g[0].K2) return gather_tile(prec, g[0]);
-  const int id = gather_cfg_multi(g, np);
-  return id >= 1 && id <= kGatherCfgs ? kGather[id].bm * 1000 + kGather[id].bn : 0;
+  return gather_id_tile(gather_cfg_multi(prec, g, np));
+}
+
+// Statistics or BN backward entries of one launch of configuration id: per
+// split-K reduce block, per row of waves of the wide halo kernel's blocks, or
+// per row tile.
+static int gather_entries(int prec, const ConvGather& g, int id) {
+  if (id == kGatherHaloW)
+    return halow_grid(g, halow_rows(prec, g)) / ceil_div(g.Cols, HALOW_BN) * HALOW_WGM;
+  if (gather_split(prec, g, id) > 1) return ceil_div(g.M, SK_ROWS);
+  return ceil_div(g.M, gather_entry(id).bm);
 }
 
 int conv_gather_stat_entries(int prec, const ConvGather& g) {
@@ -2710,28 +3550,25 @@ int conv_gather_stat_entries(int prec, const ConvGather& g) {
     const int tiles = g.N * ((g.Hm + th - 1) / th), slots = 2 * cu_count();
     return (tiles < slots ? tiles : slots) * HALO16_WAVES;
   }
-  if (gather_split(prec, g, gather_cfg(g)) > 1) return ceil_div(g.M, SK_ROWS);
-  const int bm = gather_tile(prec, g) / 1000;
-  return bm > 0 ? ceil_div(g.M, bm) : 0;
+  return gather_entries(prec, g, gather_cfg(prec, g));
 }
 
 int conv_gather_split_count(int prec, const ConvGather& g) {
   if (use_halo(prec, g) || use_halo16(prec, g)) return 1;
-  return gather_split(prec, g, gather_cfg(g));
+  return gather_split(prec, g, gather_cfg(prec, g));
 }
 
 // The BN backward partials are computed by the non-persistent gather
 // kernels and the split-K reduce (one launch of one sub-problem).
 bool conv_gather_bwd_ok(int prec, const ConvGather& g) {
   if (g.K2 || use_halo(prec, g) || use_halo16(prec, g)) return false;
-  const int id = gather_cfg(g);
-  return id >= 1 && id <= kGatherCfgs && kGather[id].kind != 2;
+  const int id = gather_cfg(prec, g);
+  return id == kGatherHaloW || gather_entry(id).kind != 2;
 }
 
 int conv_gather_bwd_entries(int prec, const ConvGather& g) {
   if (!conv_gather_bwd_ok(prec, g)) return 0;
-  const int id = gather_cfg(g);
-  return gather_split(prec, g, id) > 1 ? ceil_div(g.M, SK_ROWS) : ceil_div(g.M, kGather[id].bm);
+  return gather_entries(prec, g, gather_cfg(prec, g));
 }
 
 // Several sub-problems: the persistent kernel computes them when it runs the
@@ -2744,8 +3581,7 @@ int conv_gather_bwd_entries(int prec, const ConvGather& g) {
 bool conv_gather_bwd_ok_multi(int prec, const ConvGather* g, int np) {
   if (np == 1 && !g[0].K2) return conv_gather_bwd_ok(prec, g[0]);
   if (np < 1 || np > 4 || g[0].Cols <= 64) return false;
-  const int id = gather_cfg_multi(g, np);
-  if (id < 1 || id > kGatherCfgs || kGather[id].kind != 2) return false;
+  if (gather_entry(gather_cfg_multi(prec, g, np)).kind != 2) return false;
   const int kt = 128 / prec_bytes(prec);
   for (int i = 0; i < np; ++i)
     if (!gather_uniform(g[i], kt)) return false;
@@ -2755,7 +3591,7 @@ bool conv_gather_bwd_ok_multi(int prec, const ConvGather* g, int np) {
 int conv_gather_bwd_entries_multi(int prec, const ConvGather* g, int np) {
   if (np == 1 && !g[0].K2) return conv_gather_bwd_entries(prec, g[0]);
   if (!conv_gather_bwd_ok_multi(prec, g, np)) return 0;
-  const int bm = kGather[gather_cfg_multi(g, np)].bm;
+  const int bm = gather_entry(gather_cfg_multi(prec, g, np)).bm;
   int n = 0;
   for (int i = 0; i < np; ++i) n += g[i].M > 0 ? ceil_div(g[i].M, bm) : 0;
   return n;
