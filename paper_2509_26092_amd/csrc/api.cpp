@@ -724,7 +724,9 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
           ingest_launch(prec, images, ws + pl.x0, N, pl.H, pl.W, a.convs[0].cin_p, c->err, st));
 
   // conv + BN statistics of layer li on stream cs with the BN scratch at
-  // bnst_off / part_off
+  // bnst_off / part_off; the pass that applies the BN finishes them (bn[li])
+  // before the scratch is written again
+  std::vector<BnSrc> bn(a.convs.size());
   auto conv_bn_on = [&](int li, hipStream_t cs, size_t bnst_off, size_t part_off, bool split) -> int {
     const ConvL& L = a.convs[li];
     const ConvP& P = pl.cp[li];
@@ -745,17 +747,22 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
             (double)nc * (in_img + out_img) + (double)L.cout * P.k * P.k * P.cin * es, conv_gather_launch(prec, g, cs));
       if (train) ntiles += conv_gather_stat_entries(prec, g);
     }
-    float* mean = (float*)(ws + P.mean);
-    float* rstd = (float*)(ws + P.rstd);
-    float* sc = (float*)(ws + P.scale);
-    float* sf = (float*)(ws + P.shift);
+    BnSrc& b = bn[li];
+    b = BnSrc{};
+    b.gamma = state_c + L.g; b.beta = state_c + L.b; b.eps = eps; b.mom = mom;
+    b.mean = (float*)(ws + P.mean); b.rstd = (float*)(ws + P.rstd);
+    b.scale = (float*)(ws + P.scale); b.shift = (float*)(ws + P.shift);
     if (train) {
-      TIMED(RN18_K_BN_STATS, li, 1, "bn_stats_tiles_reduce_kernel", 0.0, (double)ntiles * L.cout * 16,
-            bn_stats_tiles_final_launch(tstats, (int)ntiles, L.cout, (double*)(ws + part_off), state_c + L.g,
-                                        state_c + L.b, eps, mom,
-                                        state_rs + L.rm, state_rs + L.rv, mean, rstd, sc, sf, cs));
+      b.rm = state_rs + L.rm; b.rv = state_rs + L.rv;
+      if (bn_stats_tiles_chunks((int)ntiles) > 1)
+        TIMED(RN18_K_BN_STATS, li, 1, "bn_stats_tiles_reduce_kernel", 0.0, (double)ntiles * L.cout * 16,
+              bn_stats_source(tstats, (int)ntiles, L.cout, (double*)(ws + part_off), &b, cs));
+      else
+        LCHK(bn_stats_source(tstats, (int)ntiles, L.cout, nullptr, &b, cs));
     } else {
-      LCHK(bn_eval_coef_launch(state_c + L.g, state_c + L.b, state_c + L.rm, state_c + L.rv, eps, L.cout, sc, sf, cs));
+      // (the pass only reads the running statistics)
+      b.kind = BnSrc::EVAL;
+      b.rm = const_cast<float*>(state_c) + L.rm; b.rv = const_cast<float*>(state_c) + L.rv;
     }
     return 0;
   };
@@ -767,14 +774,11 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
   auto apply = [&](int li, int relu, int res_mode, size_t r, int li2, size_t z, size_t mb = 0) -> int {
     const ConvL& L = a.convs[li];
     const ConvP& P = pl.cp[li];
-    const float* sc2 = li2 >= 0 ? (const float*)(ws + pl.cp[li2].scale) : nullptr;
-    const float* sf2 = li2 >= 0 ? (const float*)(ws + pl.cp[li2].shift) : nullptr;
     const double tb = (double)P.M * L.cout * es;
     TIMED(RN18_K_BN_APPLY, li, res_mode, kernel_instance_name("bn_apply_kernel", prec), 0.0,
           tb * (res_mode ? 3 : 2) + (mb ? tb / 16 : 0.0),
-          bn_apply_launch(prec, ws + P.y, (float*)(ws + P.scale), (float*)(ws + P.shift), relu, res_mode,
-                          res_mode ? ws + r : nullptr, sc2, sf2, ws + z, P.M, L.cout, st,
-                          mb ? (uint8_t*)(ws + mb) : nullptr));
+          bn_apply_launch(prec, ws + P.y, bn[li], relu, res_mode, res_mode ? ws + r : nullptr,
+                          li2 >= 0 ? bn[li2] : BnSrc{}, ws + z, P.M, L.cout, st, mb ? (uint8_t*)(ws + mb) : nullptr));
     return 0;
   };
 
@@ -785,9 +789,8 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
     const ConvP& P0 = pl.cp[0];
     TIMED(RN18_K_MAXPOOL, 0, 0, kernel_instance_name("bn_apply_pool_kernel", prec), 0.0,
           (double)N * a.convs[0].cout * ((double)pl.Hs * pl.Ws * es + (double)pl.Hp * pl.Wp * (es + 1)),
-          bn_apply_pool_launch(prec, ws + P0.y, (const float*)(ws + P0.scale), (const float*)(ws + P0.shift),
-                               ws + pl.pool, (uint8_t*)(ws + pl.parg), N, pl.Hs, pl.Ws, a.convs[0].cout, pl.Hp,
-                               pl.Wp, st));
+          bn_apply_pool_launch(prec, ws + P0.y, bn[0], ws + pl.pool, (uint8_t*)(ws + pl.parg), N, pl.Hs, pl.Ws,
+                               a.convs[0].cout, pl.Hp, pl.Wp, st));
   } else if ((r = apply(0, 1, 0, 0, -1, pl.zstem))) {
     return r;
   }
@@ -807,8 +810,8 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
     if (B.ds >= 0) {
       if (side_ds) {
         HIPCHK(hipStreamWaitEvent(st, c->ev_ds, 0));
-      } else if ((r = conv_bn(B.ds))) {
-        return r;
+      } else if ((r = conv_bn_on(B.ds, st, pl.bnst2, pl.part2, false))) {
+        return r;   // (scratch of its own: the statistics of c2 are not finished yet)
       }
       if ((r = apply(B.c2, 1, 2, pl.cp[B.ds].y, B.ds, bp.out, train ? bp.mbits : 0))) return r;
     } else {
@@ -887,13 +890,17 @@ int run_train(Ctx* c, const Plan& pl, float* state, const float* images, const i
             bn_bwd_partial_launch(prec, ws + dz, mzp, ws + P.y, (float*)(ws + P.mean), (float*)(ws + P.rstd), P.M,
                                   L.cout, part, &nblk, st, msc, msf));
     }
-    TIMED(RN18_K_BN_BWD_REDUCE, li, 1, "bn_bwd_final_kernel", 0.0, 0.0,
-          bn_bwd_final_launch(part, nblk, P.M, L.cout, state + L.g, (float*)(ws + P.rstd), grad + L.g, grad + L.b,
-                              (float*)(ws + P.coef), st));
+    const bool fold = nblk <= kBwdFoldMax;   // the apply adds the partials up itself
+    if (!fold)
+      TIMED(RN18_K_BN_BWD_REDUCE, li, 1, "bn_bwd_final_kernel", 0.0, 0.0,
+            bn_bwd_final_launch(part, nblk, P.M, L.cout, state + L.g, (float*)(ws + P.rstd), grad + L.g, grad + L.b,
+                                (float*)(ws + P.coef), st));
+    const BnBwdSrc src{part, nblk, P.M, state + L.g, (float*)(ws + P.rstd), grad + L.g, grad + L.b,
+                       fold ? nullptr : (float*)(ws + P.coef)};
     TIMED(RN18_K_BN_BWD_APPLY, li, 0, kernel_instance_name("bn_bwd_apply_kernel", prec), 0.0,
           3 * tb + (rc ? 0.0 : tb / 16),
-          bn_bwd_apply_launch(prec, ws + dz, mzp, ws + P.y, (float*)(ws + P.mean), (float*)(ws + P.coef), ws + dy,
-                              P.M, L.cout, st, msc, msf, done));
+          bn_bwd_apply_launch(prec, ws + dz, mzp, ws + P.y, (float*)(ws + P.mean), src, ws + dy, P.M, L.cout, st, msc,
+                              msf, done));
     if (!c->captures.empty()) return run_captures(c, RN18_CAP_DY, li, ws + dy, (size_t)P.M * L.cout * es);
     return 0;
   };
@@ -1530,8 +1537,11 @@ int rn18_debug_copy(rn18_ctx* h, int N, int H, int W, int which, int index, void
         // the fused stem never stores its ReLU output; recompute it from the
         // stem conv output with the coefficients of the last forward pass
         const ConvP& P0 = pl->cp[0];
-        if (bn_apply_launch(c.prec, ws + P0.y, (const float*)(ws + P0.scale), (const float*)(ws + P0.shift), 1, 0,
-                            nullptr, nullptr, nullptr, ws + pl->zstem, P0.M, a.convs[0].cout, c.stream))
+        BnSrc b{};
+        b.kind = BnSrc::STORED;
+        b.scale = (float*)(ws + P0.scale); b.shift = (float*)(ws + P0.shift);
+        if (bn_apply_launch(c.prec, ws + P0.y, b, 1, 0, nullptr, BnSrc{}, ws + pl->zstem, P0.M, a.convs[0].cout,
+                            c.stream))
           return fail(RN18_EHIP, "stem activation recompute failed");
       }
       break;

@@ -54,45 +54,27 @@ __device__ inline double block_sum_d(double v, double* sh) {
 // v - x0, sum of (v - x0)^2) of the forward conv epilogue. Every tile's sums
 // are re-referenced to one sample of the channel, K = tile 0's shift, in
 // fp64 (d = x0 - K: S1 += s1 + n d, S2 += s2 + 2 d s1 + n d^2), so the
-// tiles simply add. Stage 1: grid (channel groups of 64, tile chunks), 4
-// thread groups per block over a chunk's tiles, fixed-order combine; stage 2:
-// per channel, 4 thread groups over the chunks, fixed-order combine, then
-// mean = K + S1/M, biased variance
-// S2/M - (S1/M)^2 for normalising, unbiased (M/(M-1)) for the running one.
-// With a single chunk (at most 64 tiles) stage 1 finishes the statistics
-// itself and stage 2 is not launched.
-struct BnStatsOut {
-  const float* gamma;
-  const float* beta;
-  float eps, mom;
-  float* rm;
-  float* rv;
-  float* mean;
-  float* rstd;
-  float* scale;
-  float* shift;
-};
-
-__device__ inline void bn_stats_finish(int c, double N, double S1, double S2, double K, const BnStatsOut& o) {
-  const double m1 = S1 / N;
-  double var = S2 / N - m1 * m1;
-  if (var < 0.0) var = 0.0;
-  const double mean = K + m1;
-  const double rstd = 1.0 / sqrt(var + (double)o.eps);
-  const double sc = (double)o.gamma[c] * rstd;
-  o.mean[c] = (float)mean;
-  o.rstd[c] = (float)rstd;
-  o.scale[c] = (float)sc;
-  o.shift[c] = (float)((double)o.beta[c] - mean * sc);
-  if (o.rm) {
-    o.rm[c] = (float)((1.0 - o.mom) * (double)o.rm[c] + o.mom * mean);
-    o.rv[c] = (float)((1.0 - o.mom) * (double)o.rv[c] + o.mom * (N > 1.0 ? var * (N / (N - 1.0)) : 0.0));
-  }
+// tiles simply add; then mean = K + S1/M, biased variance S2/M - (S1/M)^2 for
+// normalising, unbiased (M/(M-1)) for the running one.
+//
+// No kernel of its own finishes them: each block of the pass that applies the
+// batch norm takes up to 64 channels (kCG) and adds up their partials itself
+// in a fixed order (64 channels x 4 thread groups), so every block gets the
+// same coefficients, and the first block of a channel group writes them for
+// the backward pass. A layer with at most 64 tile partials needs no launch
+// before it; above that bn_stats_tiles_reduce_kernel sums chunks of tiles
+// first (at most 16, so that a block reads at most 24 KB). A launch of a few
+// blocks costs 4-7 us beside its neighbours on MI355X: folding the finish took
+// the batch-64 step at 128x128 from 1.63 to 1.50 ms (evaluation of 80 images at 224x224: 0.89 to 0.83).
+__device__ inline void bn_tile_sum(const float4& p, double K, double& N, double& S1, double& S2) {
+  const double n = p.x, d = (double)p.y - K, s1 = p.z;
+  N += n;
+  S1 += s1 + n * d;
+  S2 += (double)p.w + 2.0 * d * s1 + n * d * d;
 }
 
 __global__ __launch_bounds__(256) void bn_stats_tiles_reduce_kernel(const float* __restrict__ st, int ntiles, int C,
-                                                                    int per_chunk, double* __restrict__ red,
-                                                                    BnStatsOut o) {
+                                                                    int per_chunk, double* __restrict__ red) {
   __shared__ double sh[3][4][64];
   const int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl;
@@ -101,114 +83,185 @@ __global__ __launch_bounds__(256) void bn_stats_tiles_reduce_kernel(const float*
   if (c < C) {
     const double K = (double)((const float4*)st)[c].y;
 #pragma unroll 8
-    for (int z = z0 + q; z < z1; z += 4) {
-      const float4 p = ((const float4*)st)[(long)z * C + c];
-      const double n = p.x, d = (double)p.y - K, s1 = p.z;
-      N += n;
-      S1 += s1 + n * d;
-      S2 += (double)p.w + 2.0 * d * s1 + n * d * d;
-    }
+    for (int z = z0 + q; z < z1; z += 4) bn_tile_sum(((const float4*)st)[(long)z * C + c], K, N, S1, S2);
   }
   sh[0][q][cl] = N; sh[1][q][cl] = S1; sh[2][q][cl] = S2;
   __syncthreads();
   if (q == 0 && c < C) {
-    double v[3];
+    double* out = red + ((long)blockIdx.y * C + c) * 3;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) v[k] = ((sh[k][0][cl] + sh[k][1][cl]) + sh[k][2][cl]) + sh[k][3][cl];
-    if (gridDim.y == 1) {
-      bn_stats_finish(c, v[0], v[1], v[2], (double)((const float4*)st)[c].y, o);
-    } else {
-      double* out = red + ((long)blockIdx.y * C + c) * 3;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) out[k] = v[k];
-    }
+    for (int k = 0; k < 3; ++k) out[k] = ((sh[k][0][cl] + sh[k][1][cl]) + sh[k][2][cl]) + sh[k][3][cl];
   }
 }
 
-__global__ __launch_bounds__(256) void bn_stats_tiles_final_kernel(const float* __restrict__ st,
-                                                                   const double* __restrict__ red, int nchunks, int C,
-                                                                   BnStatsOut o) {
-  __shared__ double sh[3][4][64];
-  const int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
-  double N = 0.0, S1 = 0.0, S2 = 0.0;
-  if (c < C) {
+constexpr int kCG = 64;   // channels of a block of the applying passes
+
+// Scale and shift of channels [c0, c0 + CG) into sc / sf (LDS), from the
+// source b describes; a training pass's first block (write) stores them, the
+// mean, rstd and the running statistics. All 256 threads; ends in a barrier.
+__device__ inline void bn_coefs(const BnSrc& b, int C, int c0, int CG, bool write, double (&sh)[3][4][kCG], float* sc,
+                                float* sf) {
+  const int cl = threadIdx.x & 63, q = threadIdx.x >> 6, c = c0 + cl;
+  if (b.kind == BnSrc::EVAL || b.kind == BnSrc::STORED) {
+    if (q == 0 && cl < CG) {
+      if (b.kind == BnSrc::STORED) {
+        sc[cl] = b.scale[c];
+        sf[cl] = b.shift[c];
+      } else {
+        const double rstd = 1.0 / sqrt((double)b.rv[c] + (double)b.eps);
+        const double k = (double)b.gamma[c] * rstd;
+        sc[cl] = (float)k;
+        sf[cl] = (float)((double)b.beta[c] - (double)b.rm[c] * k);
+        if (write) {
+          b.scale[c] = sc[cl];
+          b.shift[c] = sf[cl];
+        }
+      }
+    }
+    __syncthreads();
+    return;
+  }
+  double N = 0.0, S1 = 0.0, S2 = 0.0, K = 0.0;
+  float ga = 0.f, be = 0.f;
+  if (cl < CG) {
+    ga = b.gamma[c];
+    be = b.beta[c];
+    K = (double)((const float4*)b.st)[c].y;
+    if (b.kind == BnSrc::TILES) {
+#pragma unroll 8
+      for (int z = q; z < b.n; z += 4) bn_tile_sum(((const float4*)b.st)[(long)z * C + c], K, N, S1, S2);
+    } else {
 #pragma unroll 4
-    for (int r = q; r < nchunks; r += 4) {
-      const double* p = red + ((long)r * C + c) * 3;
-      N += p[0];
-      S1 += p[1];
-      S2 += p[2];
+      for (int z = q; z < b.n; z += 4) {
+        const double* p = b.red + ((long)z * C + c) * 3;
+        N += p[0];
+        S1 += p[1];
+        S2 += p[2];
+      }
     }
   }
   sh[0][q][cl] = N; sh[1][q][cl] = S1; sh[2][q][cl] = S2;
   __syncthreads();
-  if (q != 0 || c >= C) return;
-  N = ((sh[0][0][cl] + sh[0][1][cl]) + sh[0][2][cl]) + sh[0][3][cl];
-  S1 = ((sh[1][0][cl] + sh[1][1][cl]) + sh[1][2][cl]) + sh[1][3][cl];
-  S2 = ((sh[2][0][cl] + sh[2][1][cl]) + sh[2][2][cl]) + sh[2][3][cl];
-  bn_stats_finish(c, N, S1, S2, (double)((const float4*)st)[c].y, o);
-}
-
-
-template <typename T>
-__global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y, const float* __restrict__ scale,
-                                                       const float* __restrict__ shift, int relu, int res_mode,
-                                                       const T* __restrict__ r, const float* __restrict__ scale2,
-                                                       const float* __restrict__ shift2, T* __restrict__ z,
-                                                       long nchunks, int C, uint8_t* __restrict__ mbits) {
-  constexpr int VW = TT<T>::VW;
-  __shared__ float sc[kMaxC], sf[kMaxC], sc2[kMaxC], sf2[kMaxC];
-  for (int c = threadIdx.x; c < C; c += 256) {
-    sc[c] = scale[c];
-    sf[c] = shift[c];
-    if (res_mode == 2) { sc2[c] = scale2[c]; sf2[c] = shift2[c]; }
+  if (q == 0 && cl < CG) {
+    N = ((sh[0][0][cl] + sh[0][1][cl]) + sh[0][2][cl]) + sh[0][3][cl];
+    S1 = ((sh[1][0][cl] + sh[1][1][cl]) + sh[1][2][cl]) + sh[1][3][cl];
+    S2 = ((sh[2][0][cl] + sh[2][1][cl]) + sh[2][2][cl]) + sh[2][3][cl];
+    const double m1 = S1 / N;
+    double var = S2 / N - m1 * m1;
+    if (var < 0.0) var = 0.0;
+    const double mean = K + m1;
+    const double rstd = 1.0 / sqrt(var + (double)b.eps);
+    const double k = (double)ga * rstd;
+    const float fs = (float)k, ff = (float)((double)be - mean * k);
+    sc[cl] = fs;
+    sf[cl] = ff;
+    if (write) {
+      b.mean[c] = (float)mean;
+      b.rstd[c] = (float)rstd;
+      b.scale[c] = fs;
+      b.shift[c] = ff;
+      if (b.rm) {
+        b.rm[c] = (float)((1.0 - b.mom) * (double)b.rm[c] + b.mom * mean);
+        b.rv[c] = (float)((1.0 - b.mom) * (double)b.rv[c] + b.mom * (N > 1.0 ? var * (N / (N - 1.0)) : 0.0));
+      }
+    }
   }
   __syncthreads();
-  const int cpr = C / VW;
-  for (long q = blockIdx.x * 256l + threadIdx.x; q < nchunks; q += (long)gridDim.x * 256) {
-    const int c0 = (int)(q % cpr) * VW;
-    float v[VW];
-    unpack<T>(((const uint4*)y)[q], v);
-#pragma unroll
-    for (int e = 0; e < VW; ++e) v[e] = bn_affine(v[e], sc[c0 + e], sf[c0 + e]);
-    if (res_mode == 1) {
-      float w[VW];
-      unpack<T>(((const uint4*)r)[q], w);
-#pragma unroll
-      for (int e = 0; e < VW; ++e) v[e] += w[e];
-    } else if (res_mode == 2) {
-      float w[VW];
-      unpack<T>(((const uint4*)r)[q], w);
-#pragma unroll
-      for (int e = 0; e < VW; ++e) v[e] += w[e] * sc2[c0 + e] + sf2[c0 + e];
-    }
-    if (relu) {
-#pragma unroll
-      for (int e = 0; e < VW; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-    }
-    const uint4 pk = pack<T>(v);
-    ((uint4*)z)[q] = pk;
-    if (mbits) {
-      // bit e: element e of the chunk as stored is > 0 (its ReLU mask)
-      float vr[VW];
-      unpack<T>(pk, vr);
-      uint32_t b = 0;
-#pragma unroll
-      for (int e = 0; e < VW; ++e) b |= (vr[e] > 0.f ? 1u : 0u) << e;
-      mbits[q] = (uint8_t)b;
-    }
-  }
 }
 
-__global__ void bn_eval_coef_kernel(const float* gamma, const float* beta, const float* rm, const float* rv,
-                                    float eps, int C, float* scale, float* shift) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
-  const double rstd = 1.0 / sqrt((double)rv[c] + (double)eps);
-  const double s = (double)gamma[c] * rstd;
-  scale[c] = (float)s;
-  shift[c] = (float)((double)beta[c] - (double)rm[c] * s);
+// Block geometry of the applying passes: block b takes channel group b %
+// groups and every (blocks / groups)-th step of rpi rows, four steps at a time;
+// a thread keeps its channels, so their coefficients live in registers. The
+// first loads are issued before the coefficients are known, so that the sums
+// of the partials run while they arrive.
+struct RowWalk {
+  int CG, cpr, c0, cc, rr, rpi, rb, nrb;   // group channels, chunks per row, first channel, chunk, row, rows per step
+  __device__ inline RowWalk(int C, int VW) {
+    CG = min(kCG, C);
+    const int groups = C / CG, cpg = CG / VW, g = blockIdx.x % groups;
+    cpr = C / VW;
+    c0 = g * CG;
+    cc = g * cpg + (int)threadIdx.x % cpg;
+    rr = threadIdx.x / cpg;
+    rpi = 256 / cpg;
+    rb = blockIdx.x / groups;
+    nrb = gridDim.x / groups;
+  }
+};
+constexpr int kRowsU = 4;   // rows per thread and step
+
+// z = act(bn(y) [+ r] [+ bn2(r)]): RES 0, 1, 2. The pass is an HBM stream (2
+// or 3 tensors).
+template <typename T, int RES>
+__global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ y, BnSrc b1, int relu,
+                                                       const T* __restrict__ r, BnSrc b2, T* __restrict__ z, long M,
+                                                       int C, uint8_t* __restrict__ mbits) {
+  constexpr int VW = TT<T>::VW, U = kRowsU;
+  __shared__ double sh[3][4][kCG];
+  __shared__ float lsc[kCG], lsf[kCG], lsc2[kCG], lsf2[kCG];
+  const RowWalk w(C, VW);
+  const long step = (long)w.nrb * w.rpi;
+  struct Rows { uint4 y[U], r[RES ? U : 1]; };
+  auto at = [&](long row) { return (uint32_t)(row * w.cpr + w.cc); };
+  auto load = [&](long r0, Rows& d) {   // (rows past the end load the last row)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = at(min(r0 + u * step, M - 1));
+      d.y[u] = ((const uint4*)y)[i];
+      if constexpr (RES != 0) d.r[u] = ((const uint4*)r)[i];
+    }
+  };
+  long r0 = (long)w.rb * w.rpi + w.rr;
+  Rows d;
+  load(r0, d);
+  bn_coefs(b1, C, w.c0, w.CG, w.rb == 0, sh, lsc, lsf);
+  if constexpr (RES == 2) bn_coefs(b2, C, w.c0, w.CG, w.rb == 0, sh, lsc2, lsf2);
+  const int cl = w.cc * VW - w.c0;
+  float sc[VW], sf[VW], sc2[VW], sf2[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    sc[e] = lsc[cl + e];
+    sf[e] = lsf[cl + e];
+    sc2[e] = RES == 2 ? lsc2[cl + e] : 0.f;
+    sf2[e] = RES == 2 ? lsf2[cl + e] : 0.f;
+  }
+  auto process = [&](long r0, const Rows& d) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r0 + u * step >= M) break;
+      const uint32_t i = at(r0 + u * step);
+      float v[VW];
+      unpack<T>(d.y[u], v);
+#pragma unroll
+      for (int e = 0; e < VW; ++e) v[e] = bn_affine(v[e], sc[e], sf[e]);
+      if constexpr (RES != 0) {
+        float x[VW];
+        unpack<T>(d.r[u], x);
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] += RES == 1 ? x[e] : x[e] * sc2[e] + sf2[e];
+      }
+      if (relu) {
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+      }
+      const uint4 pk = pack<T>(v);
+      ((uint4*)z)[i] = pk;
+      if (mbits) {
+        // bit e: element e of the chunk as stored is > 0 (its ReLU mask)
+        float vr[VW];
+        unpack<T>(pk, vr);
+        uint32_t bits = 0;
+#pragma unroll
+        for (int e = 0; e < VW; ++e) bits |= (vr[e] > 0.f ? 1u : 0u) << e;
+        mbits[i] = (uint8_t)bits;
+      }
+    }
+  };
+  while (r0 < M) {
+    process(r0, d);
+    r0 += U * step;
+    if (r0 < M) load(r0, d);
+  }
 }
 
 template <typename T>
@@ -311,40 +364,110 @@ __global__ __launch_bounds__(256) void bn_bwd_final_kernel(const float* __restri
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__ dz, const uint8_t* __restrict__ mb,
-                                                           const T* __restrict__ y, const float* __restrict__ mean,
-                                                           const float* __restrict__ coef,
-                                                           const float* __restrict__ mscale,
-                                                           const float* __restrict__ mshift, T* __restrict__ dy,
-                                                           long nchunks, int C) {
-  constexpr int VW = TT<T>::VW;
-  __shared__ float k1[kMaxC], k2[kMaxC], k3[kMaxC], mu[kMaxC], msc[kMaxC], msf[kMaxC];
-  for (int c = threadIdx.x; c < C; c += 256) {
-    k1[c] = coef[3 * c];
-    k2[c] = coef[3 * c + 1];
-    k3[c] = coef[3 * c + 2];
-    mu[c] = mean[c];
-    if (mscale) { msc[c] = mscale[c]; msf[c] = mshift[c]; }
+// Coefficients of the backward apply for channels [c0, c0 + CG) into k1, k2,
+// k3 (LDS): from coef when the finish kernel ran, else from the partials, added
+// up by every block (see bn_coefs); the first block of a channel group stores
+// dgamma and dbeta. All 256 threads; ends in a barrier.
+__device__ inline void bn_bwd_coefs(const BnBwdSrc& b, int C, int c0, int CG, bool write, double (&sh)[3][4][kCG],
+                                    float* k1, float* k2, float* k3) {
+  const int cl = threadIdx.x & 63, q = threadIdx.x >> 6, c = c0 + cl;
+  if (b.coef) {
+    if (q == 0 && cl < CG) {
+      k1[cl] = b.coef[3 * c];
+      k2[cl] = b.coef[3 * c + 1];
+      k3[cl] = b.coef[3 * c + 2];
+    }
+    __syncthreads();
+    return;
+  }
+  double s1 = 0.0, s2 = 0.0;
+  float ga = 0.f, rs1 = 0.f;
+  if (cl < CG) {
+    ga = b.gamma[c];
+    rs1 = b.rstd[c];
+#pragma unroll 8
+    for (int z = q; z < b.n; z += 4) {
+      const float2 p = ((const float2*)b.part)[(long)z * C + c];
+      s1 += p.x;
+      s2 += p.y;
+    }
+  }
+  sh[0][q][cl] = s1; sh[1][q][cl] = s2;
+  __syncthreads();
+  if (q == 0 && cl < CG) {
+    s1 = ((sh[0][0][cl] + sh[0][1][cl]) + sh[0][2][cl]) + sh[0][3][cl];
+    s2 = ((sh[1][0][cl] + sh[1][1][cl]) + sh[1][2][cl]) + sh[1][3][cl];
+    const double rs = (double)rs1, kk = (double)ga * rs;
+    k1[cl] = (float)kk;
+    k2[cl] = (float)(-kk * rs * s2 / (double)b.M);
+    k3[cl] = (float)(-kk * s1 / (double)b.M);
+    if (write) {
+      b.dbeta[c] = (float)s1;
+      b.dgamma[c] = (float)s2;
+    }
   }
   __syncthreads();
-  const int cpr = C / VW;
-  for (long q = blockIdx.x * 256l + threadIdx.x; q < nchunks; q += (long)gridDim.x * 256) {
-    const int c0 = (int)(q % cpr) * VW;
-    float g[VW], yy[VW], o[VW];
-    unpack<T>(((const uint4*)dz)[q], g);
-    unpack<T>(((const uint4*)y)[q], yy);
-    if (mb) {
-      const uint32_t m = mb[q];
+}
+
+// dy = k1 g + k2 (y - mean) + k3, g = dz where the ReLU passed: MASK 0 none, 1
+// mask bytes, 2 recomputed from y. An HBM stream (3 tensors).
+template <typename T, int MASK>
+__global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__ dz, const uint8_t* __restrict__ mb,
+                                                           const T* __restrict__ y, const float* __restrict__ mean,
+                                                           BnBwdSrc b, const float* __restrict__ mscale,
+                                                           const float* __restrict__ mshift, T* __restrict__ dy,
+                                                           long M, int C) {
+  constexpr int VW = TT<T>::VW, U = kRowsU;
+  __shared__ double sh[3][4][kCG];
+  __shared__ float l1[kCG], l2[kCG], l3[kCG];
+  const RowWalk w(C, VW);
+  const long step = (long)w.nrb * w.rpi;
+  struct Rows { uint4 g[U], y[U]; uint32_t m[U]; };
+  auto at = [&](long row) { return (uint32_t)(row * w.cpr + w.cc); };
+  auto load = [&](long r0, Rows& d) {   // (rows past the end load the last row)
 #pragma unroll
-      for (int e = 0; e < VW; ++e) g[e] = (m >> e) & 1u ? g[e] : 0.f;
-    } else if (mscale) {
-#pragma unroll
-      for (int e = 0; e < VW; ++e) g[e] = relu_stored<T>(yy[e], msc[c0 + e], msf[c0 + e]) > 0.f ? g[e] : 0.f;
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = at(min(r0 + u * step, M - 1));
+      d.g[u] = ((const uint4*)dz)[i];
+      d.y[u] = ((const uint4*)y)[i];
+      d.m[u] = MASK == 1 ? mb[i] : 0u;
     }
+  };
+  long r0 = (long)w.rb * w.rpi + w.rr;
+  Rows d;
+  load(r0, d);
+  bn_bwd_coefs(b, C, w.c0, w.CG, w.rb == 0, sh, l1, l2, l3);
+  const int c0 = w.cc * VW, cl = c0 - w.c0;
+  float k1[VW], k2[VW], k3[VW], mu[VW], msc[VW], msf[VW];
 #pragma unroll
-    for (int e = 0; e < VW; ++e) o[e] = k1[c0 + e] * g[e] + k2[c0 + e] * (yy[e] - mu[c0 + e]) + k3[c0 + e];
-    ((uint4*)dy)[q] = pack<T>(o);
+  for (int e = 0; e < VW; ++e) {
+    k1[e] = l1[cl + e];
+    k2[e] = l2[cl + e];
+    k3[e] = l3[cl + e];
+    mu[e] = mean[c0 + e];
+    msc[e] = MASK == 2 ? mscale[c0 + e] : 0.f;
+    msf[e] = MASK == 2 ? mshift[c0 + e] : 0.f;
+  }
+  auto process = [&](long r0, const Rows& d) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r0 + u * step >= M) break;
+      float g[VW], yy[VW], o[VW];
+      unpack<T>(d.g[u], g);
+      unpack<T>(d.y[u], yy);
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        if constexpr (MASK == 1) g[e] = (d.m[u] >> e) & 1u ? g[e] : 0.f;
+        if constexpr (MASK == 2) g[e] = relu_stored<T>(yy[e], msc[e], msf[e]) > 0.f ? g[e] : 0.f;
+        o[e] = k1[e] * g[e] + k2[e] * (yy[e] - mu[e]) + k3[e];
+      }
+      ((uint4*)dy)[at(r0 + u * step)] = pack<T>(o);
+    }
+  };
+  while (r0 < M) {
+    process(r0, d);
+    r0 += U * step;
+    if (r0 < M) load(r0, d);
   }
 }
 
@@ -357,14 +480,13 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__
 // with the ReLU mask recomputed from y by the same arithmetic.
 
 template <typename T>
-__global__ __launch_bounds__(256) void bn_apply_pool_kernel(const T* __restrict__ y, const float* __restrict__ scale,
-                                                            const float* __restrict__ shift, T* __restrict__ pool,
+__global__ __launch_bounds__(256) void bn_apply_pool_kernel(const T* __restrict__ y, BnSrc b, T* __restrict__ pool,
                                                             uint8_t* __restrict__ arg, int N, int H, int W, int C,
                                                             int Ho, int Wo) {
   constexpr int VW = TT<T>::VW;
+  __shared__ double sh[3][4][kCG];
   __shared__ float sc[kMaxC], sf[kMaxC];
-  for (int c = threadIdx.x; c < C; c += 256) { sc[c] = scale[c]; sf[c] = shift[c]; }
-  __syncthreads();
+  for (int c0 = 0; c0 < C; c0 += kCG) bn_coefs(b, C, c0, min(kCG, C - c0), blockIdx.x == 0, sh, sc + c0, sf + c0);
   const int cpr = C / VW;
   const int total = N * Ho * Wo * cpr;
   for (int q = blockIdx.x * 256 + threadIdx.x; q < total; q += gridDim.x * 256) {
@@ -523,23 +645,45 @@ inline int ok() { return hipGetLastError() == hipSuccess ? 0 : -4; }
 
 }  // namespace
 
-int bn_apply_launch(int prec, const void* y, const float* scale, const float* shift, int relu, int res_mode,
-                    const void* r, const float* scale2, const float* shift2, void* z, long M, int C, hipStream_t s,
-                    uint8_t* mbits) {
-  const long nchunks = M * C / prec_vw(prec);
+namespace {
+// Blocks of an applying pass: at most 8 per CU of 256 CUs (each adds up its
+// channels' partials first), four rows per thread and step.
+int row_blocks(int prec, long M, int C) {
+  const int CG = C < kCG ? C : kCG, groups = C / CG, rpi = 256 / (CG / prec_vw(prec));
+  long b = (M + (long)rpi * kRowsU - 1) / ((long)rpi * kRowsU);
+  if (b * groups < 512) {
+    // small tensors: fewer rows per thread, up to two blocks per CU
+    const long b1 = (M + rpi - 1) / rpi, lim = 512 / groups;
+    b = b1 < lim ? b1 : lim;
+  }
+  const long cap = 2048 / groups;
+  if (b > cap) b = cap;
+  if (b < 1) b = 1;
+  return (int)b * groups;
+}
+bool row_shape_ok(int prec, long M, int C) {
+  const int vw = prec_vw(prec), CG = C < kCG ? C : kCG;
+  return C % vw == 0 && C % CG == 0 && 256 % (CG / vw) == 0 && M * (C / vw) < (1l << 31);
+}
+}  // namespace
+
+int bn_apply_launch(int prec, const void* y, const BnSrc& b, int relu, int res_mode, const void* r, const BnSrc& b2,
+                    void* z, long M, int C, hipStream_t s, uint8_t* mbits) {
+  if (!row_shape_ok(prec, M, C)) return -1;
+  const dim3 grid(row_blocks(prec, M, C)), block(256);
   return with_prec(prec, [&](auto tag) {
     using T = decltype(tag);
-    hipLaunchKernelGGL(bn_apply_kernel<T>, dim3(stream_blocks(nchunks)), dim3(256), 0, s, (const T*)y, scale, shift,
-                       relu, res_mode, (const T*)r, scale2, shift2, (T*)z, nchunks, C, mbits);
+    if (res_mode == 0)
+      hipLaunchKernelGGL((bn_apply_kernel<T, 0>), grid, block, 0, s, (const T*)y, b, relu, (const T*)r, b2, (T*)z, M, C,
+                         mbits);
+    else if (res_mode == 1)
+      hipLaunchKernelGGL((bn_apply_kernel<T, 1>), grid, block, 0, s, (const T*)y, b, relu, (const T*)r, b2, (T*)z, M, C,
+                         mbits);
+    else
+      hipLaunchKernelGGL((bn_apply_kernel<T, 2>), grid, block, 0, s, (const T*)y, b, relu, (const T*)r, b2, (T*)z, M, C,
+                         mbits);
     return ok();
   });
-}
-
-int bn_eval_coef_launch(const float* gamma, const float* beta, const float* rm, const float* rv, float eps, int C,
-                        float* scale, float* shift, hipStream_t s) {
-  hipLaunchKernelGGL(bn_eval_coef_kernel, dim3((C + 255) / 256), dim3(256), 0, s, gamma, beta, rm, rv, eps, C, scale,
-                     shift);
-  return ok();
 }
 
 int bn_bwd_partial_blocks(int prec, long M, int C) {
@@ -571,32 +715,38 @@ int bn_bwd_final_launch(const float* part, int nblk, long M, int C, const float*
   return ok();
 }
 
-int bn_bwd_apply_launch(int prec, const void* dz, const uint8_t* mb, const void* y, const float* mean, const float* coef,
-                        void* dy, long M, int C, hipStream_t s, const float* mscale, const float* mshift,
-                        hipEvent_t done) {
-  const long nchunks = M * C / prec_vw(prec);
+int bn_bwd_apply_launch(int prec, const void* dz, const uint8_t* mb, const void* y, const float* mean,
+                        const BnBwdSrc& b, void* dy, long M, int C, hipStream_t s, const float* mscale,
+                        const float* mshift, hipEvent_t done) {
+  if (!row_shape_ok(prec, M, C)) return -1;
+  const dim3 grid(row_blocks(prec, M, C)), block(256);
   return with_prec(prec, [&](auto tag) {
     using T = decltype(tag);
-    if (done) {
-      // the event completes with this kernel: no separate marker on the queue
-      hipExtLaunchKernelGGL(bn_bwd_apply_kernel<T>, dim3(stream_blocks(nchunks)), dim3(256), 0, s, nullptr, done, 0,
-                            (const T*)dz, mb, (const T*)y, mean, coef, mscale, mshift, (T*)dy, nchunks, C);
-    } else {
-      hipLaunchKernelGGL(bn_bwd_apply_kernel<T>, dim3(stream_blocks(nchunks)), dim3(256), 0, s, (const T*)dz, mb,
-                         (const T*)y, mean, coef, mscale, mshift, (T*)dy, nchunks, C);
-    }
+    auto launch = [&](auto kernel) {
+      // (with done, the event completes with this kernel: no separate marker on the queue)
+      if (done)
+        hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, done, 0, (const T*)dz, mb, (const T*)y, mean, b,
+                              mscale, mshift, (T*)dy, M, C);
+      else
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, (const T*)dz, mb, (const T*)y, mean, b, mscale, mshift, (T*)dy, M,
+                           C);
+    };
+    if (mb) launch(bn_bwd_apply_kernel<T, 1>);
+    else if (mscale) launch(bn_bwd_apply_kernel<T, 2>);
+    else launch(bn_bwd_apply_kernel<T, 0>);
     return ok();
   });
 }
 
-int bn_apply_pool_launch(int prec, const void* y, const float* scale, const float* shift, void* pool, uint8_t* arg,
-                         int N, int H, int W, int C, int Ho, int Wo, hipStream_t s) {
+int bn_apply_pool_launch(int prec, const void* y, const BnSrc& b, void* pool, uint8_t* arg, int N, int H, int W, int C,
+                         int Ho, int Wo, hipStream_t s) {
   const int vw = prec_vw(prec);
   if (C > kMaxC || (long)N * H * W * (C / vw) >= (1l << 31)) return -1;  // 32-bit chunk indices
   const long total = (long)N * Ho * Wo * (C / vw);
+  const int blocks = stream_blocks(total);
   return with_prec(prec, [&](auto tag) {
     using T = decltype(tag);
-    hipLaunchKernelGGL(bn_apply_pool_kernel<T>, dim3(stream_blocks(total)), dim3(256), 0, s, (const T*)y, scale, shift,
+    hipLaunchKernelGGL(bn_apply_pool_kernel<T>, dim3(blocks < 2048 ? blocks : 2048), dim3(256), 0, s, (const T*)y, b,
                        (T*)pool, arg, N, H, W, C, Ho, Wo);
     return ok();
   });
@@ -632,21 +782,23 @@ int bn_bwd_apply_pool_launch(int prec, const void* dpool, const uint8_t* arg, co
 }
 
 int bn_stats_tiles_chunks(int ntiles) {
-  int r = (ntiles + 63) / 64;
-  return r < 1 ? 1 : r > 64 ? 64 : r;
+  const int r = (ntiles + 63) / 64;
+  return r < 1 ? 1 : r > 16 ? 16 : r;
 }
 
-int bn_stats_tiles_final_launch(const float* tile_stats, int ntiles, int C, double* scratch, const float* gamma,
-                                const float* beta, float eps, float momentum, float* run_mean, float* run_var,
-                                float* mean, float* rstd, float* scale, float* shift, hipStream_t s) {
+int bn_stats_source(const float* tile_stats, int ntiles, int C, double* scratch, BnSrc* b, hipStream_t s) {
   const int chunks = bn_stats_tiles_chunks(ntiles);
-  const int per_chunk = (ntiles + chunks - 1) / chunks;
-  const BnStatsOut o{gamma, beta, eps, momentum, run_mean, run_var, mean, rstd, scale, shift};
+  b->st = tile_stats;
+  if (chunks == 1) {
+    b->kind = BnSrc::TILES;
+    b->n = ntiles;
+    return 0;
+  }
+  b->kind = BnSrc::CHUNKS;
+  b->red = scratch;
+  b->n = chunks;
   hipLaunchKernelGGL(bn_stats_tiles_reduce_kernel, dim3((C + 63) / 64, chunks), dim3(256), 0, s, tile_stats, ntiles,
-                     C, per_chunk, scratch, o);
-  if (chunks > 1)
-    hipLaunchKernelGGL(bn_stats_tiles_final_kernel, dim3((C + 63) / 64), dim3(256), 0, s, tile_stats, scratch, chunks,
-                       C, o);
+                     C, (ntiles + chunks - 1) / chunks, scratch);
   return ok();
 }
 

@@ -124,24 +124,53 @@ int wgrad_reduce_launch(const float* P, int splits, int Cout, int KHW, int Cin, 
 // Batch norm (per-channel over M = N*H*W rows of an [M][C] tensor)
 // ---------------------------------------------------------------------------
 // partial sums of (y - pivot) and (y - pivot)^2 per block; pivot = y[0][c]
-// Batch statistics from the forward conv epilogue's per-tile partials
-// (rows, shift, sum of v - shift, sum of (v - shift)^2) [ntiles][C][4].
-// scratch: bn_stats_tiles_chunks(ntiles) * C * 3 doubles
+// Where an applying pass gets a BN's scale and shift from: the tile partials of
+// the forward conv epilogue (rows, shift, sum of v - shift, sum of (v -
+// shift)^2) [n][C][4], sums over n chunks of them, the running statistics, or
+// stored coefficients. From partials the pass also stores mean, rstd, scale
+// and shift and updates the running statistics.
+struct BnSrc {
+  enum { TILES = 0, CHUNKS = 1, EVAL = 2, STORED = 3 };
+  int kind, n;
+  const float* st;       // tile partials (TILES; tile 0's shift for CHUNKS)
+  const double* red;     // chunk sums [n][C][3]
+  const float* gamma;
+  const float* beta;
+  float eps, mom;
+  float* rm;             // running statistics (updated from partials unless null; read by EVAL)
+  float* rv;
+  float* mean;
+  float* rstd;
+  float* scale;
+  float* shift;
+};
+// Fill b's source from a conv's tile partials: directly (up to 64 tiles), or
+// summed into chunks by a launch first. scratch: bn_stats_tiles_chunks(ntiles)
+// * C * 3 doubles.
 int bn_stats_tiles_chunks(int ntiles);
-int bn_stats_tiles_final_launch(const float* tile_stats, int ntiles, int C, double* scratch, const float* gamma,
-                                const float* beta, float eps, float momentum, float* run_mean, float* run_var,
-                                float* mean, float* rstd, float* scale, float* shift, hipStream_t s);
-// z = act(y*scale+shift [+ r] [+ (yd*scale2+shift2)])
-//  res_mode: 0 none, 1 identity residual r, 2 projected residual (yd, scale2, shift2)
+int bn_stats_source(const float* tile_stats, int ntiles, int C, double* scratch, BnSrc* b, hipStream_t s);
+// z = act(bn(y) [+ r] [+ bn2(r)]); res_mode: 0 none, 1 identity residual r, 2
+// projected residual (r with its own BN b2)
 // ReLU mask bytes (mbits, optional, M*C/VW bytes): one byte per 16-byte
 // storage chunk of z (VW = 8 bf16 or 4 fp32 elements), bit e set iff element
 // e of the chunk as stored is > 0.
-int bn_apply_launch(int prec, const void* y, const float* scale, const float* shift, int relu,
-                    int res_mode, const void* r, const float* scale2, const float* shift2,
+int bn_apply_launch(int prec, const void* y, const BnSrc& b, int relu, int res_mode, const void* r, const BnSrc& b2,
                     void* z, long M, int C, hipStream_t s, uint8_t* mbits = nullptr);
-// eval-mode BN coefficients from running statistics
-int bn_eval_coef_launch(const float* gamma, const float* beta, const float* rm, const float* rv,
-                        float eps, int C, float* scale, float* shift, hipStream_t s);
+// Where the backward apply gets its coefficients from: n partials [n][C][2]
+// (it then also stores dgamma and dbeta), or coef when bn_bwd_final_launch ran.
+struct BnBwdSrc {
+  const float* part;
+  int n;
+  long M;
+  const float* gamma;
+  const float* rstd;
+  float* dgamma;
+  float* dbeta;
+  const float* coef;
+};
+// Partials that every block of the apply adds up itself: with more, the finish
+// kernel runs first.
+constexpr int kBwdFoldMax = 128;
 // backward partials of g = dz*mask (or dz): sum g, sum g*(y-mean)*rstd
 // The ReLU mask comes from mask bytes mb (the layout bn_apply_launch writes)
 // when given; with mb = NULL and mscale set it is recomputed as
@@ -159,8 +188,8 @@ int bn_bwd_partial_pool_blocks(int prec, int N, int H, int W, int C);
 // ImageNet stem fused with its max pool (y = stem conv output [N][H][W][C],
 // pool / arg = pool output and argmax [N][Ho][Wo][C]): forward BN-apply +
 // ReLU + pool; backward BN reduce / apply reading the pooled gradient.
-int bn_apply_pool_launch(int prec, const void* y, const float* scale, const float* shift, void* pool, uint8_t* arg,
-                         int N, int H, int W, int C, int Ho, int Wo, hipStream_t s);
+int bn_apply_pool_launch(int prec, const void* y, const BnSrc& b, void* pool, uint8_t* arg, int N, int H, int W, int C,
+                         int Ho, int Wo, hipStream_t s);
 int bn_bwd_partial_pool_launch(int prec, const void* dpool, const uint8_t* arg, const void* y, const float* scale,
                                const float* shift, const float* mean, const float* rstd, int N, int H, int W, int C,
                                int Ho, int Wo, float* part, int* nblk, hipStream_t s);
@@ -172,7 +201,7 @@ int bn_bwd_final_launch(const float* part, int nblk, long M, int C, const float*
 // dy = k1*g + k2*(y-mean) + k3; done (optional) is recorded by the kernel
 // launch itself, completing when the kernel does
 int bn_bwd_apply_launch(int prec, const void* dz, const uint8_t* mb, const void* y, const float* mean,
-                        const float* coef, void* dy, long M, int C, hipStream_t s, const float* mscale = nullptr,
+                        const BnBwdSrc& b, void* dy, long M, int C, hipStream_t s, const float* mscale = nullptr,
                         const float* mshift = nullptr, hipEvent_t done = nullptr);
 
 // ---------------------------------------------------------------------------
