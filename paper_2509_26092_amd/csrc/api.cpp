@@ -708,12 +708,14 @@ int run_forward(Ctx* c, const Plan& pl, const float* state_c, float* state_rs, c
   auto W = [&](int li) { return (const char*)c->wf + (size_t)pl.cp[li].wf * c->es; };
 
   const double es = c->es;
+  // (evaluation has no use for the data-gradient layout; every training step rebuilds both)
+  void* const wd = train ? c->wd : nullptr;
   TIMED(RN18_K_PREP, -1, 2, kernel_instance_name("repack_tiled_kernel", prec), 0.0,
-        (double)(a.wf_total - c->tab_total) * (4.0 + 2.0 * es),
-        repack_tiled_launch(prec, state_c, c->wf, c->wd, c->tab + c->ntab, c->nttab, c->ntiles, st));
+        (double)(a.wf_total - c->tab_total) * (4.0 + (train ? 2.0 : 1.0) * es),
+        repack_tiled_launch(prec, state_c, c->wf, wd, c->tab + c->ntab, c->nttab, c->ntiles, st));
   if (c->tab_total > 0)
     TIMED(RN18_K_PREP, -1, 0, kernel_instance_name("repack_kernel", prec), 0.0, (double)c->tab_total * (4.0 + 2.0 * es),
-          repack_launch(prec, state_c, c->wf, c->wd, c->tab, c->ntab, c->tab_total, st));
+          repack_launch(prec, state_c, c->wf, wd, c->tab, c->ntab, c->tab_total, st));
   if (pl.cp[0].s2d)
     TIMED(RN18_K_PREP, -1, 1, kernel_instance_name("ingest_s2d_kernel", prec), 0.0,
           (double)N * pl.H * pl.W * (12.0 + 4.0 * es),
