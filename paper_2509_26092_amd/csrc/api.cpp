@@ -624,7 +624,7 @@ int launch_wgrad_part(int prec, const void* dy, const void* x, float* wpart, int
   g.pix_per_split = pps;
   g.splits = splits;
   const double mpix = (double)N * Ho * Wo;
-  int pi = PROF_BEGIN(c, RN18_K_CONV_WGRAD, layer, conv_wgrad_tile(prec, Cout, g.Kcols), conv_wgrad_kernel_name_shape(prec, g),
+  int pi = PROF_BEGIN(c, RN18_K_CONV_WGRAD, layer, conv_wgrad_tile(prec, Cout, g.Kcols, g.Mpix), conv_wgrad_kernel_name_shape(prec, g),
                       2.0 * Cout * (s2d ? 49 : k * k) * cin_real * mpix,
                       (double)splits * Cout * g.Kcols * 4);
   int r = conv_wgrad_launch(prec, g, st);

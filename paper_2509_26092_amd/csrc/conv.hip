@@ -2553,6 +2553,185 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_wgrad2_kernel(ConvWgrad g
 }
 
 // ---------------------------------------------------------------------------
+// Weight gradient, half-stage pipelined (16-bit). What bounds the kernel above
+// is LDS: the transposing reads deliver 128 bytes a clock per CU, and its 64x32
+// wave tiles need 192 for full-rate MFMAs, with 64 more written by the loads.
+// Here a block of 8 waves takes 128 output channels x 256 columns as 64x64 wave
+// tiles (128 bytes a clock read, 48 written); the fragments of the next half
+// stage are read between the MFMAs of this one, and all three ring buffers are
+// in flight. (128x64 wave tiles with the waves split over K would read 96, but
+// their accumulators and fragments do not fit 256 registers beside the
+// transposing reads: 178 spills.) The columns are the first MFMA operand, so a
+// lane stores 16 bytes of consecutive columns. One block per CU: it is for long
+// pixel ranges (wgrad_cfg).
+// ---------------------------------------------------------------------------
+constexpr int WG3_BM = 128, WG3_BN = 256, WG3_STAGES = 3;
+template <typename T>
+__global__ __launch_bounds__(512, 2) void conv_wgrad3_kernel(ConvWgrad g) {
+  constexpr int NW = 8, WGN = 4, CPS = 64, KP = 64, SA = WG3_BM / CPS, SB = WG3_BN / CPS, IPW = SA + SB;
+  constexpr int SUB_B = KP * 128, STAGE_B = (SA + SB) * SUB_B, STAGES = WG3_STAGES;
+  constexpr int FM = WG3_BM / 2 / 16, FN = WG3_BN / WGN / 16, NF = FM + FN, NM = FM * FN;
+  static_assert(KP / 8 == NW, "a wave's loads fill the same 8 pixel rows of every sub-tile");
+  static_assert(STAGES * STAGE_B <= 163840, "LDS");
+  __shared__ uint4 smem[STAGES * STAGE_B / 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;     // channel sub-tile, column sub-tile of this wave
+  // (split, tile), tile fastest: see conv_wgrad2_kernel
+  const int tiles_n = (g.Kcols + WG3_BN - 1) / WG3_BN;
+  const int tiles = ((g.Cout + WG3_BM - 1) / WG3_BM) * tiles_n;
+  const int lt = xcd_remap(blockIdx.x, gridDim.x);
+  const int split = lt / tiles, t = lt - split * tiles;
+  const int co0 = (t / tiles_n) * WG3_BM, k0 = (t % tiles_n) * WG3_BN;
+  const int p_begin = split * g.pix_per_split;
+  const int p_end = min(g.Mpix, p_begin + g.pix_per_split);
+  const uint32_t smem_lds = lds_addr(smem);
+  const i32x4_t rsA = buffer_rsrc(g.DY, (uint32_t)((long)g.Mpix * g.Cout * 2));
+  const i32x4_t rsB = buffer_rsrc(g.X, (uint32_t)((long)g.N * g.H * g.W * g.Cin * 2));
+
+  // ---- loads: load u of this wave fills pixel rows 8 wave .. + 7 of sub-tile u
+  // (dY, then the columns' input channels); the lane's 16 bytes go to slot lane
+  // % 8 of row lane / 8 and hold chunk (lane % 8) ^ (row % 8)
+  const int row = wave * 8 + (lane >> 3), c = (lane & 7) ^ (lane >> 3);
+  uint32_t coff[IPW];   // channel (and tap) byte offset, or out of range
+  int tdh[SB], tdw[SB];
+#pragma unroll
+  for (int u = 0; u < SA; ++u) {
+    const int co = co0 + u * CPS + c * 8;
+    coff[u] = co < g.Cout ? (uint32_t)(co * 2) : kOutOfRange;
+  }
+#pragma unroll
+  for (int u = 0; u < SB; ++u) {
+    const int kc = k0 + u * CPS + c * 8;
+    coff[SA + u] = kOutOfRange;
+    tdh[u] = tdw[u] = 0;
+    if (kc < g.Kcols) {
+      const int tap = kc / g.Cin, ci = kc - tap * g.Cin, kh = tap / g.KW, kw = tap - kh * g.KW;
+      tdh[u] = kh - g.pad;
+      tdw[u] = kw - g.pad;
+      coff[SA + u] = (uint32_t)(((kh - g.pad) * g.W + (kw - g.pad)) * g.Cin * 2 + ci * 2);
+    }
+  }
+  // the pixel of this lane's row advances by KP per stage, in (n, ho, wo) digits
+  const int HWo = g.Ho * g.Wo;
+  int pn = (p_begin + row) / HWo, pho = (p_begin + row - pn * HWo) / g.Wo, pwo = p_begin + row - pn * HWo - pho * g.Wo;
+  const int adv_n = KP / HWo, adv_r = KP - adv_n * HWo, adv_ho = adv_r / g.Wo, adv_wo = adv_r - adv_ho * g.Wo;
+  int p_issue = p_begin;
+  uint32_t ld_base = 0, ld_y = 0, ld_x = 0;
+  int ld_h = 0, ld_w = 0;
+  bool ld_in = false;
+  // (a stage past the range loads zeros and counts as issued)
+  auto stage_begin = [&](uint32_t ring) {
+    ld_base = smem_lds + ring;
+    ld_in = p_issue + row < p_end;
+    ld_y = (uint32_t)((p_issue + row) * g.Cout * 2);
+    ld_h = pho * g.stride;
+    ld_w = pwo * g.stride;
+    ld_x = (uint32_t)(((pn * g.H + ld_h) * g.W + ld_w) * g.Cin * 2);
+    p_issue += KP;
+    pwo += adv_wo;
+    pho += adv_ho;
+    pn += adv_n;
+    if (pwo >= g.Wo) { pwo -= g.Wo; ++pho; }
+    if (pho >= g.Ho) { pho -= g.Ho; ++pn; }
+  };
+  auto stage_load = [&](int u) {
+    const uint32_t dst = ld_base + (uint32_t)(u * SUB_B + wave * 1024);
+    if (u < SA) {
+      lds_dma16_buf((ld_in & (coff[u] != kOutOfRange)) ? ld_y + coff[u] : kOutOfRange, rsA, dst);
+    } else {
+      const bool in = ld_in & (coff[u] != kOutOfRange) & ((unsigned)(ld_h + tdh[u - SA]) < (unsigned)g.H) &
+                      ((unsigned)(ld_w + tdw[u - SA]) < (unsigned)g.W);
+      lds_dma16_buf(in ? ld_x + coff[u] : kOutOfRange, rsB, dst);
+    }
+  };
+
+  // ---- operand fragments: 16 channels x the 32 pixels of a half stage, as two
+  // transposing reads of four pixels (WOp::frag)
+  const int r16 = lane & 15, kq = lane >> 4;
+  const uint32_t lane0 = (uint32_t)((8 * kq + (r16 >> 2)) * 128 +
+                                    ((((r16 & 3) >> 1) ^ (r16 >> 2)) << 4) + ((r16 & 1) << 3));
+  const lds_char_t* const lds = (const lds_char_t*)(lds_void_t)smem;
+  auto tr = [&](uint32_t at) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) v4i16_t*)(lds + at)));
+  };
+  uint4 a0[FM], b0[FN], a1[FM], b1[FN];
+  // at: the lane's offset in the stage, made opaque per stage so that the
+  // fragments' addresses are recomputed rather than held in registers
+  auto read_frag = [&](int f, uint32_t at, int half, uint4(&a)[FM], uint4(&b)[FN]) {
+    const uint32_t x = at ^ (uint32_t)((f < FN ? f : f - FN) * 32);
+    const uint32_t sub = (uint32_t)((f < FN ? SA + wn : wm) * SUB_B + half * 4096);
+    const uint2 lo = tr(x + sub), hi = tr((x ^ 64u) + sub + 512u);
+    const uint4 q = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    if (f < FN) b[f] = q;
+    else a[f - FN] = q;
+  };
+  auto stage_at = [&](uint32_t st) {
+    uint32_t at = lane0 + st;
+    asm volatile("" : "+v"(at));
+    return at;
+  };
+  floatx4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // the MFMAs of one half stage with extra(e), e < NP, spread between pairs of them
+  auto half = [&](const uint4(&a)[FM], const uint4(&b)[FN], auto np, auto&& extra) {
+    constexpr int NP = decltype(np)::value;
+#pragma unroll
+    for (int m = 0; m < NM; m += 2) {
+#pragma unroll
+      for (int e = 0; e < NP; ++e)
+        if (e * NM / NP >= m && e * NM / NP < m + 2) extra(e);
+      __builtin_amdgcn_sched_barrier(0);
+      Mma<T>::run(acc[m / FN][m % FN], b[m % FN], a[m / FN], 0);
+      Mma<T>::run(acc[(m + 1) / FN][(m + 1) % FN], b[(m + 1) % FN], a[(m + 1) / FN], 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  const int S = p_end > p_begin ? (p_end - p_begin + KP - 1) / KP : 0;
+#pragma unroll
+  for (int q = 0; q < STAGES; ++q) {
+    stage_begin((uint32_t)(q * STAGE_B));
+#pragma unroll
+    for (int u = 0; u < IPW; ++u) stage_load(u);
+  }
+  wait_vmcnt<(STAGES - 1) * IPW>();
+  barrier_only();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) read_frag(f, lane0, 0, a0, b0);
+  uint32_t st = 0;
+  for (int s = 0; s < S; ++s) {
+    const uint32_t at = stage_at(st);
+    half(a0, b0, std::integral_constant<int, NF>{}, [&](int f) { read_frag(f, at, 1, a1, b1); });
+    // stage s + 1 has landed and everybody has read stage s, whose buffer takes stage s + STAGES
+    wait_vmcnt<(STAGES - 2) * IPW>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    barrier_only();
+    stage_begin(st);
+    st = st == (uint32_t)((STAGES - 1) * STAGE_B) ? 0u : st + (uint32_t)STAGE_B;
+    const uint32_t nx = stage_at(st);
+    half(a1, b1, std::integral_constant<int, NF + IPW>{}, [&](int e) {
+      if (e < 2 * IPW && e % 2) stage_load(e / 2);
+      else read_frag(e < 2 * IPW ? e / 2 : e - IPW, nx, 0, a0, b0);
+    });
+  }
+  wait_vmcnt<0>();
+  float* __restrict__ P = g.P + (long)split * g.Cout * g.Kcols;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int co = co0 + wm * 64 + i * 16 + r16;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int kc = k0 + wn * 64 + j * 16 + 4 * kq;
+      if (co < g.Cout && kc < g.Kcols) *(floatx4_t*)(P + (long)co * g.Kcols + kc) = acc[i][j];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Halo weight gradient for the 64 -> 64 channel 3x3 stride-1 convolutions
 // (bf16). A block walks row strips (up to 256 output pixels of whole rows of
 // one image); per strip it stages the strip's dY rows and the input patch
@@ -3369,31 +3548,60 @@ int launch_wgrad2(const ConvWgrad& g, hipStream_t s) {
 //   1-3: register-transposing kernel 16x64, 64x64, 128x128
 //   4: 64x128 1x4 s2   5: 64x128 2x2 s2   6: 128x128 2x2 s2   7: 128x128 2x2 s3
 //   8: 64x64 2x2 s2    9: 128x64 2x2 s2  10: 128x128 2x4 s2
-constexpr int kWgradCfgs = 10;
+//  11: 128x256 2x4, half-stage pipelined (automatic choice only)
+constexpr int kWgradCfgs = 10, kWgrad3 = 11;
 int g_wgrad_override = 0;
 
 // Choice measured on MI355X (bf16 224x224 batch 256, fp32 32x32 batch 128).
-int wgrad_cfg(int prec, int Cout, int Kcols) {
+// The pipelined 128x256 tile runs one block per CU, one round of them: its
+// split count fills the CUs once (at least three quarters of them), within the
+// 32 MB of partials that the 128x128 tile's have, and a block needs at least 24
+// stages of 64 pixels to pay for its prologue. Measured with the reduction (us,
+// 128x128 before): 200704 pixels, 128 x 1152: 78 (88); 50176, 256 x 2304: 71
+// (75); 12544, 512 x 4608: 76 (80); 200704, 128 x 576: 54 (78); 33263, 320 x
+// 1728: 58 (74); at 20 stages 32768, 256 x 1152: 36 (34). The batch-256 step at
+// 224x224: 5.87 -> 5.75 ms.
+constexpr int kWgrad3MinStages = 24;
+int wgrad3_splits(int Cout, int Kcols, long Mpix) {
+  const int tiles = ceil_div(Cout, WG3_BM) * ceil_div(Kcols, WG3_BN);
+  const long cus = cu_count() > 0 ? cu_count() : 256;
+  long k = cus / tiles;
+  const long by_bytes = (32l << 20) / ((long)Cout * Kcols * 4);
+  if (k > by_bytes) k = by_bytes;
+  if (k < 1 || k * tiles * 4 < cus * 3 || Mpix / k < 64 * kWgrad3MinStages) return 0;
+  return (int)k;
+}
+
+int wgrad_cfg(int prec, int Cout, int Kcols, long Mpix) {
   if (g_wgrad_override) return g_wgrad_override;
   if (Cout <= 16) return 1;
   if (prec != PREC_F32) {
+    if (Cout >= 128 && Kcols >= 256 && wgrad3_splits(Cout, Kcols, Mpix) > 0) return kWgrad3;
     if (Cout <= 64) return 4;
     return Kcols <= 576 ? 9 : 10;
   }
   return Cout <= 64 ? 8 : 6;
 }
 
-void wgrad_tile(int prec, int Cout, int Kcols, int* bm, int* bn) {
-  static const int tile[kWgradCfgs + 1][2] = {{0, 0},   {16, 64},  {64, 64},  {128, 128}, {64, 128}, {64, 128},
-                                              {128, 128}, {128, 128}, {64, 64}, {128, 64},  {128, 128}};
-  const int id = wgrad_cfg(prec, Cout, Kcols);
+void wgrad_tile(int prec, int Cout, int Kcols, long Mpix, int* bm, int* bn) {
+  static const int tile[kWgrad3 + 1][2] = {{0, 0},     {16, 64},  {64, 64}, {128, 128}, {64, 128},  {64, 128},
+                                           {128, 128}, {128, 128}, {64, 64}, {128, 64},  {128, 128}, {WG3_BM, WG3_BN}};
+  const int id = wgrad_cfg(prec, Cout, Kcols, Mpix);
   *bm = tile[id][0];
   *bn = tile[id][1];
 }
 
 template <typename T>
 int wgrad_dispatch(const ConvWgrad& g, hipStream_t s) {
-  switch (wgrad_cfg(prec_of<T>(), g.Cout, g.Kcols)) {
+  const int id = wgrad_cfg(prec_of<T>(), g.Cout, g.Kcols, g.Mpix);
+  if constexpr (sizeof(T) == 2) {
+    if (id == kWgrad3) {
+      const int tiles = ceil_div(g.Cout, WG3_BM) * ceil_div(g.Kcols, WG3_BN);
+      hipLaunchKernelGGL(conv_wgrad3_kernel<T>, dim3(tiles * g.splits), dim3(512), 0, s, g);
+      return hipGetLastError() == hipSuccess ? 0 : -4;
+    }
+  }
+  switch (id) {
     case 1: return launch_wgrad<T, 16, 64, 1, 4>(g, s);
     case 2: return launch_wgrad<T, 64, 64, 2, 2>(g, s);
     case 3: return launch_wgrad<T, 128, 128, 2, 2>(g, s);
@@ -3501,12 +3709,13 @@ const char* gather_kernel_name(int prec, const ConvGather& g, int id) {
   return intern_name(buf);
 }
 
-const char* conv_wgrad_kernel_name(int prec, int Cout, int Kcols) {
+const char* conv_wgrad_kernel_name(int prec, int Cout, int Kcols, long Mpix) {
   static const int cfg[kWgradCfgs + 1][6] = {
       {0, 0, 0, 0, 0, 0},     {1, 16, 64, 1, 4, 0},   {1, 64, 64, 2, 2, 0},  {1, 128, 128, 2, 2, 0},
       {2, 64, 128, 1, 4, 2},  {2, 64, 128, 2, 2, 2},  {2, 128, 128, 2, 2, 2}, {2, 128, 128, 2, 2, 3},
       {2, 64, 64, 2, 2, 2},   {2, 128, 64, 2, 2, 2},  {2, 128, 128, 2, 4, 2}};
-  const int id = wgrad_cfg(prec, Cout, Kcols);
+  const int id = wgrad_cfg(prec, Cout, Kcols, Mpix);
+  if (id == kWgrad3) return kernel_instance_name("conv_wgrad3_kernel", prec);
   if (id < 1 || id > kWgradCfgs) return "conv_wgrad_kernel";
   const int* c = cfg[id];
   char buf[128];
@@ -3615,9 +3824,9 @@ int conv_wgrad_override(int id) {
   return 0;
 }
 
-int conv_wgrad_tile(int prec, int Cout, int Kcols) {
+int conv_wgrad_tile(int prec, int Cout, int Kcols, long Mpix) {
   int bm, bn;
-  wgrad_tile(prec, Cout, Kcols, &bm, &bn);
+  wgrad_tile(prec, Cout, Kcols, Mpix, &bm, &bn);
   return bm * 1000 + bn;
 }
 
@@ -3634,7 +3843,7 @@ int conv_gather_launch_multi(int prec, const ConvGather* g, int np, hipStream_t 
 int conv_wgrad_splits(int prec, int Cout, int Kcols, long Mpix, int* pix_per_split) {
   const int ktp = 128 / prec_bytes(prec);
   int bm, bn;
-  wgrad_tile(prec, Cout, Kcols, &bm, &bn);
+  wgrad_tile(prec, Cout, Kcols, Mpix, &bm, &bn);
   const long tiles = (long)ceil_div(Cout, bm) * ceil_div(Kcols, bn);
   long splits = (1024 + tiles - 1) / tiles;
   const long per_split_bytes = (long)Cout * Kcols * 4;
@@ -3644,6 +3853,7 @@ int conv_wgrad_splits(int prec, int Cout, int Kcols, long Mpix, int* pix_per_spl
   if (max_by_len < 1) max_by_len = 1;
   if (splits > max_by_bytes) splits = max_by_bytes;
   if (splits > max_by_len) splits = max_by_len;
+  if (wgrad_cfg(prec, Cout, Kcols, Mpix) == kWgrad3) splits = wgrad3_splits(Cout, Kcols, Mpix);
   if (splits < 1) splits = 1;
   long pps = (Mpix + splits - 1) / splits;
   pps = (pps + ktp - 1) / ktp * ktp;
@@ -3663,7 +3873,7 @@ int conv_wgrad_splits_shape(int prec, const ConvWgrad& g, int* pix_per_split) {
 
 const char* conv_wgrad_kernel_name_shape(int prec, const ConvWgrad& g) {
   if (use_wgrad_halo(prec, g)) return prec == PREC_F16 ? "conv_wgrad_halo_kernel<_Float16>" : "conv_wgrad_halo_kernel<bf16>";
-  return conv_wgrad_kernel_name(prec, g.Cout, g.KH * g.KW * g.Cin);
+  return conv_wgrad_kernel_name(prec, g.Cout, g.KH * g.KW * g.Cin, (long)g.N * g.Ho * g.Wo);
 }
 
 int conv_wgrad_launch(int prec, const ConvWgrad& g, hipStream_t s) {

@@ -95,14 +95,14 @@ struct ConvWgrad {
   int Mpix, Kcols, pix_per_split, splits;
 };
 int conv_wgrad_launch(int prec, const ConvWgrad& g, hipStream_t s);
-int conv_wgrad_tile(int prec, int Cout, int Kcols);
+int conv_wgrad_tile(int prec, int Cout, int Kcols, long Mpix);
 // Names of the kernel instance a launch would use, in the form a profiler's
 // demangler prints them (namespace dropped, uint16_t storage shown as bf16);
 // kernel_instance_name(base, prec) is base<bf16> or base<float>.
 const char* conv_gather_kernel_name(int prec, const ConvGather& g);
 const char* conv_gather_kernel_name_multi(int prec, const ConvGather* g, int np);
 int conv_gather_tile_multi(int prec, const ConvGather* g, int np);
-const char* conv_wgrad_kernel_name(int prec, int Cout, int Kcols);
+const char* conv_wgrad_kernel_name(int prec, int Cout, int Kcols, long Mpix);
 const char* kernel_instance_name(const char* base, int prec);
 // Force one weight-gradient configuration (0 = automatic choice).
 int conv_wgrad_override(int id);
