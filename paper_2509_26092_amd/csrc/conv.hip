@@ -662,6 +662,13 @@ constexpr int gather_occupancy(int bm, int bn, int nw, int stages) {
 // Statistics: sums over a wave's pixels with DPP adds within the 16 lanes that
 // hold the same channels, then over the waves of a tile through LDS.
 //
+// What bounds it: LDS. A 64x32 wave tile wants 192 bytes of operands a clock
+// per CU at the full MFMA rate, and reads deliver about 195 with nothing else
+// in the pipe; so the larger wave tiles where the grid fills them, and deep
+// rings where it does not. Forward or data gradient alone (us, two-stage
+// 128x128 tiles with reads before MFMAs first): 3136 x 512, K 4608, bf16 (64 x
+// 7 x 7): 38 -> 31; 32000 x 128, K 1152, fp32: 82 -> 74.
+//
 // Uniform row layout only (gather_uniform).
 // ---------------------------------------------------------------------------
 // Pixel rows of a stage in LDS: whole 8-row load instructions for every wave
@@ -1045,7 +1052,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, gather_occupancy(gather_rp_row
 //
 // Operand order, weight rows, swizzles and the half-stage loop are those of
 // conv_gather_rp_kernel; so is the order of the K sum (channel blocks outer,
-// taps inner), and with it every result bit.
+// taps inner), and with it every result bit. 200704 x 128, K 1152, bf16 (256 x
+// 28 x 28), forward alone: 69 -> 65 us; the pure MFMA time is about 41.
 // ---------------------------------------------------------------------------
 struct ConvHaloW {
   ConvGather g;
@@ -1211,7 +1219,7 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
       const bool last = cb + 1 == CB, live = !last || more;
       const int xn = last ? nn : n, xi0 = last ? ni0 : i0, xcb = last ? 0 : cb + 1;
       const uint32_t xbuf = pbuf ^ (uint32_t)PB;
-      static_assert(PB == 0xC000, "");
+      static_assert(PB == 0xC000, "the patch read offsets assume 48 KB buffers");
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         asm volatile("" : "+s"(pw));
@@ -3559,8 +3567,9 @@ int g_wgrad_override = 0;
 // stages of 64 pixels to pay for its prologue. Measured with the reduction (us,
 // 128x128 before): 200704 pixels, 128 x 1152: 78 (88); 50176, 256 x 2304: 71
 // (75); 12544, 512 x 4608: 76 (80); 200704, 128 x 576: 54 (78); 33263, 320 x
-// 1728: 58 (74); at 20 stages 32768, 256 x 1152: 36 (34). The batch-256 step at
-// 224x224: 5.87 -> 5.75 ms.
+// 1728: 58 (74); at 20 stages 32768, 256 x 1152: 36 (34). Those operands come
+// from HBM, as in a step; where they stay in the Infinity Cache between calls
+// the first shape takes 71 (69). The batch-256 step at 224x224: 5.87 -> 5.75 ms.
 constexpr int kWgrad3MinStages = 24;
 int wgrad3_splits(int Cout, int Kcols, long Mpix) {
   const int tiles = ceil_div(Cout, WG3_BM) * ceil_div(Kcols, WG3_BN);
