@@ -3074,6 +3074,11 @@ int cu_count() {
   if (!n[dev] && hipDeviceGetAttribute(&n[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n[dev] = 0;
   return n[dev];
 }
+// Compute units that a choice of kernel is made for (256 without a GPU).
+int plan_cus() {
+  const int n = cu_count();
+  return n > 0 ? n : 256;
+}
 
 // A second K segment must have whole channel blocks, A2 shaped like A and
 // B2 [Cols][Cin], within the 32-bit buffer offsets.
@@ -3217,6 +3222,7 @@ int halow_rows(int prec, const ConvGather& g) {
   if ((long)g.N * g.Hin * g.Win * g.Cin * 2 >= (1l << 31) || (long)g.M * g.Cols * 2 >= (1l << 31) ||
       (long)g.Cols * 9 * g.Cin * 2 >= (1l << 31) || (long)g.N * (g.Hm + 1) >= (1l << 30))
     return 0;
+  if (ceil_div(g.Cols, HALOW_BN) > plan_cus()) return 0;   // a block keeps its column tile: one block per tile at least
   // as many whole rows as fit 256 pixels and the patch, with one zero row
   // between the images that a tile touches; at least 192 pixels keep the MFMA
   // tiles filled (and the statistics entries, four per block, at most one per
@@ -3233,7 +3239,7 @@ int halow_rows(int prec, const ConvGather& g) {
 }
 int halow_grid(const ConvGather& g, int th) {
   const int tiles_n = ceil_div(g.Cols, HALOW_BN), tiles = ceil_div((long)g.N * g.Hm, th) * tiles_n;
-  const int most = cu_count() / tiles_n * tiles_n;   // a block keeps its column tile
+  const int most = plan_cus() / tiles_n * tiles_n;   // a block keeps its column tile
   return tiles < most ? tiles : most;
 }
 
@@ -3379,7 +3385,7 @@ float gather_est(int prec, const GatherCost& e, long tiles, int S, long cus, boo
 int gather_best(int prec, const ConvGather& g, int* split) {
   const int S = ceil_div(g.K, 128 / prec_bytes(prec));
   const bool can_split = g.ws && ((uintptr_t)g.ws & 15) == 0 && g_gather_split != 1 && !g.K2;
-  const long cus = cu_count() > 0 ? cu_count() : 256;
+  const long cus = plan_cus();
   const bool operands = g.mode != 0 || g.bstats;
   int best = 0;
   float tb = 0.f;
@@ -3573,7 +3579,7 @@ int g_wgrad_override = 0;
 constexpr int kWgrad3MinStages = 24;
 int wgrad3_splits(int Cout, int Kcols, long Mpix) {
   const int tiles = ceil_div(Cout, WG3_BM) * ceil_div(Kcols, WG3_BN);
-  const long cus = cu_count() > 0 ? cu_count() : 256;
+  const long cus = plan_cus();
   long k = cus / tiles;
   const long by_bytes = (32l << 20) / ((long)Cout * Kcols * 4);
   if (k > by_bytes) k = by_bytes;

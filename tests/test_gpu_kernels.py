@@ -39,6 +39,17 @@ def test_wide_halo(case, direction):
     forced(34, direction, "bf16", case)
 
 
+@pytest.mark.parametrize("direction", [op.test_conv_fwd, op.test_conv_dgrad], ids=["fwd", "dgrad"])
+def test_more_column_tiles_than_compute_units(direction):
+    """One 16x16 image whose columns make one 128-column tile more than there
+    are compute units (a block of the wide halo kernel keeps its columns, so
+    that kernel cannot take it): launched by another kernel, not refused."""
+    import torch
+    wide = 128 * torch.cuda.get_device_properties(0).multi_processor_count + 8
+    cin, cout = (64, wide) if direction is op.test_conv_fwd else (wide, 64)
+    direction("bf16", (1, cin, cin, 16, 16, cout, 3, 1, 1))
+
+
 @pytest.mark.parametrize("cfg", [3, 4, 5, 6, 8, 10, 11, 12, 17, 18, 19, 20, 21, 22])
 @pytest.mark.parametrize("case", [
     (1, 64, 64, 3, 3, 72, 3, 1, 1),         # 9 rows in any tile, 72 columns
@@ -86,3 +97,4 @@ def test_average_pool_sizes():
             # fp32 sums in another tile order, through at most 18 layers
             assert torch.allclose(one[0], out[i], rtol=1e-4, atol=1e-4 * float(out.abs().max())), (arch, i)
         w.close()
+
