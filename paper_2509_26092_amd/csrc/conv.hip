@@ -3423,10 +3423,16 @@ bool gather_short(int prec, const ConvGather& g) { return g.K <= 4 * (128 / prec
 int gather_auto(int prec, const ConvGather& g) {
   if (g.Cols <= 32 || !gather_uniform(g, 128 / prec_bytes(prec))) return gather_plain(g);
   if (g.Cols <= 64) {
-    // 64 columns: 256x64 tiles where they fill the chip, else 64x64 (fp32,
-    // 147456 rows, K 576: 64x64 95 us, 256x64 121 us; 131072 rows: 83 and 81)
-    const long t256 = ceil_div(g.M, 256);
-    if (prec == PREC_F32) return t256 % 512 == 0 || t256 >= 2048 ? 22 : 9;
+    if (prec == PREC_F32) {
+      // 64 columns: the fp32 MFMAs bound both tiles alike, so the time follows
+      // the fullest CU: 256x64 tiles (less LDS traffic) where they give it no
+      // more rows than 64x64 tiles do, from two resident blocks on. K 576, us,
+      // 256x64 / 64x64 tiles (rows in units of 256): 448 85 / 79, 464 86 / 89,
+      // 512 86 / 89, 516 123 / 99, 960 161 / 153, 1024 162 / 165, 2080 351 / 323.
+      const long cus = plan_cus();
+      const long s256 = (ceil_div(g.M, 256) + cus - 1) / cus * 4, s64 = (ceil_div(g.M, 64) + cus - 1) / cus;
+      return s256 >= 8 && s256 <= s64 ? 22 : 9;
+    }
     return g.M >= 131072 ? 22 : g.M >= 65536 ? 3 : 9;
   }
   if (gather_short(prec, g)) return gather_plain(g);

@@ -98,3 +98,38 @@ def test_average_pool_sizes():
             assert torch.allclose(one[0], out[i], rtol=1e-4, atol=1e-4 * float(out.abs().max())), (arch, i)
         w.close()
 
+
+def step_kernels(arch, classes, prec, n, h, cls):
+    """Layer and kernel name of every launch of one class in a training step."""
+    import torch
+    from oracle import net
+    from paper_2509_26092_amd import inputs
+    L = net.Layout(arch, classes)
+    w = B.Worker(arch, classes, prec)
+    st = torch.from_numpy(net.init_state(L, 3).astype(np.float32)).cuda()
+    x = torch.from_numpy(inputs.images(4, n, h, h)).cuda()
+    y = torch.from_numpy(inputs.labels(4, n, classes)).cuda()
+    B.rn18_profile_enable(w.ctx, True)
+    w.train_step(st, x, y, 0.1, torch.zeros(1, device="cuda"))
+    recs = [(r["layer"], r["kernel"]) for r in B.rn18_profile_read(w.ctx) if r["cls"] == cls]
+    w.close()
+    return L, recs
+
+
+@pytest.mark.parametrize("n", [127, 128, 129, 520])
+def test_choice_of_64_column_tiles(n):
+    """Full precision, 64 columns: the matrix units bound both tiles alike, so
+    the 256x64 tile runs only where the fullest compute unit gets no more work
+    than with 64x64 tiles, and nearly equal grids get the same kernel."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    L, recs = step_kernels("cifar", 10, "fp32", n, 32, "conv_fwd")
+    names = [k for layer, k in recs if 1 <= layer <= 4]
+    assert len(names) == 4 and len(set(names)) == 1, names
+    M = n * 32 * 32
+    share = {"64, 64": -(-(-(-M // 64)) // cus), "256, 64": 4 * -(-(-(-M // 256)) // cus)}
+    tile = next(t for t in share if "<float, %s," % t in names[0])
+    assert share[tile] == min(share.values()), (names[0], share)
+    if cus == 256 and n in (127, 128):
+        assert tile == "256, 64", names[0]
+
