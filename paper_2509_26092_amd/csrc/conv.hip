@@ -3350,13 +3350,16 @@ int gather_cfg(int prec, const ConvGather& g) {
 // two resident 128x128 blocks hide an epilogue with operands best (200704 x
 // 128, K 1152: 34 70, 16 81; with a residual 16 87, 34 93; 50176 x 256, K
 // 2304: 12 60, 17 62, 16 75; 12544 x 512, K 4608: 11 61, 34 62, 16 71).
+// The deep rings (10, 8) are considered for grids of one round only: with more
+// rounds they took 17% and 7% more than the estimate (median of 88 and 76
+// layers; 11160 x 320, K 2880: 10 55 us, 11 43, 16 47).
 // In fp32 the MFMAs bound every tile alike: the choice spreads the tiles most
 // evenly over the CUs, weighted by the measured share of the MFMA rate (f: with
 // one resident block, c[0]: with more). 36864 x 128, K 1152: 9 99 us, 16 147.
-struct GatherCost { int id, bmax; float f, h, c[5]; };
+struct GatherCost { int id, bmax; float f, h, c[5]; bool one = false; };   // one: grids of a single round only
 constexpr GatherCost kCost16[] = {
-    {14, 5, 1.f, 1.3f, {.62f, .66f, .68f, .72f, .88f}}, {10, 2, 1.5f, 1.9f, {.28f, .32f}},
-    {20, 3, 5.f, 5.f, {.50f, .58f, .69f}},              {8, 1, 3.f, 4.3f, {.46f}},
+    {14, 5, 1.f, 1.3f, {.62f, .66f, .68f, .72f, .88f}}, {10, 2, 1.5f, 1.9f, {.28f, .32f}, true},
+    {20, 3, 5.f, 5.f, {.50f, .58f, .69f}},              {8, 1, 3.f, 4.3f, {.46f}, true},
     {16, 2, 6.f, 4.f, {.50f, .76f}},                    {11, 1, 9.5f, 8.5f, {.60f}},
     {5, 1, 7.5f, 9.f, {.71f}},                          {6, 1, 10.f, 9.f, {.64f}},
     {12, 1, 15.5f, 10.f, {1.05f}},                      {18, 1, 16.5f, 10.f, {1.16f}},
@@ -3400,12 +3403,13 @@ int gather_best(int prec, const ConvGather& g, int* split) {
       const GatherCfg& c = gather_entry(e.id);
       tiles = (long)ceil_div(g.M, c.bm) * ceil_div(g.Cols, c.bn);
     }
+    if (e.one && tiles > cus * e.bmax) return;
     const float t = gather_est(prec, e, tiles, S, cus, operands);
     if (!best || t < tb) { best = e.id; tb = t; *split = 1; }
     if (!can_split || e.id == kGatherHaloW || tiles > kSplitMaxTiles) return;
     const double mn = (double)g.M * g.Cols * 4;
     for (int k = 2; k <= 8 && S / k >= kSplitMinStages; ++k) {
-      if (mn * k > (double)g.ws_bytes) break;
+      if (mn * k > (double)g.ws_bytes || (e.one && tiles * k > cus * e.bmax)) break;
       const float ts = gather_est(prec, e, tiles * k, ceil_div(S, k), cus, operands) + 4.f + (float)(mn * (k + 1) / 3.5e6);
       if (ts < tb) { best = e.id; tb = ts; *split = k; }
     }
@@ -3417,8 +3421,17 @@ int gather_best(int prec, const ConvGather& g, int* split) {
   return best;
 }
 
-// At most four stages of K: the plain loop (see kCost16).
-bool gather_short(int prec, const ConvGather& g) { return g.K <= 4 * (128 / prec_bytes(prec)); }
+// Short K, the plain loop: at most four stages (see kCost16), and in 16 bits up
+// to eight where 128x128 tiles fill the chip and the rows are not the wide halo
+// kernel's (1x1 layers: with so few stages a round is mostly its stores, which
+// the estimate doesn't know. 45480 x 320, us: K 320 37 estimated best, 32
+// plain; K 512 48 and 43; 31500 x 320, K 384 29 and 26).
+bool gather_short(int prec, const ConvGather& g) {
+  const int kt = 128 / prec_bytes(prec);
+  if (g.K <= 4 * kt) return true;
+  return prec != PREC_F32 && g.K <= 8 * kt && (long)ceil_div(g.M, 128) * ceil_div(g.Cols, 128) >= plan_cus() &&
+         halow_rows(prec, g) == 0;
+}
 
 int gather_auto(int prec, const ConvGather& g) {
   if (g.Cols <= 32 || !gather_uniform(g, 128 / prec_bytes(prec))) return gather_plain(g);
@@ -3433,7 +3446,10 @@ int gather_auto(int prec, const ConvGather& g) {
       const long s256 = (ceil_div(g.M, 256) + cus - 1) / cus * 4, s64 = (ceil_div(g.M, 64) + cus - 1) / cus;
       return s256 >= 8 && s256 <= s64 ? 22 : 9;
     }
-    return g.M >= 131072 ? 22 : g.M >= 65536 ? 3 : 9;
+    // (16 bits: the plain loop; the pipelined tiles of the same shapes are 1-7%
+    // slower whether operands come from L2, the Infinity Cache or HBM: 53100
+    // rows, K 4608: 67 us against 70; 134640, K 2304: 83 and 85)
+    return gather_plain(g);
   }
   if (gather_short(prec, g)) return gather_plain(g);
   int split;

@@ -133,3 +133,20 @@ def test_choice_of_64_column_tiles(n):
     if cus == 256 and n in (127, 128):
         assert tile == "256, 64", names[0]
 
+
+def test_deep_rings_run_one_round():
+    """The deep-ring tiles (16-bit 64x64 and 128x128, four stages) are for
+    grids that one round of resident blocks covers."""
+    import torch
+    from gpu_util import tensor_shapes
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    deep = {"<bf16, 64, 64, 2, 2, 1, 4>": (64, 64, 2), "<bf16, 128, 128, 2, 4, 1, 4>": (128, 128, 1)}
+    for n, h in ((96, 224), (256, 192), (64, 128)):
+        L, recs = step_kernels("imagenet", 10, "bf16", n, h, "conv_fwd")
+        shapes = tensor_shapes(L, n, h)
+        for layer, kernel in recs:
+            for name, (bm, bn, per_cu) in deep.items():
+                if kernel.endswith(name):
+                    _, c, ho, wo = shapes[("y", L.convs[layer][0])]
+                    tiles = -(-n * ho * wo // bm) * -(-c // bn)
+                    assert tiles <= per_cu * cus, (n, h, layer, kernel, tiles)
