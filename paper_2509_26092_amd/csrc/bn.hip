@@ -12,6 +12,8 @@
 // HBM streams with the per-channel coefficients staged in LDS.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "pool.h"
 
@@ -646,17 +648,21 @@ inline int ok() { return hipGetLastError() == hipSuccess ? 0 : -4; }
 }  // namespace
 
 namespace {
-// Blocks of an applying pass: at most 8 per CU of 256 CUs (each adds up its
-// channels' partials first), four rows per thread and step.
+// Blocks of an applying pass: at most 8 per CU (each adds up its channels'
+// partials first), four rows per thread and step. Alone, large tensors are
+// slower than with one row per thread, 32 blocks per CU and coefficients that a
+// launch of their own finished (802816 x 64 in bf16: 48 us against 42, with a
+// residual 69 and 60, backward 68 and 60), but whole training steps are not:
+// batch 256 at 224x224 5.93 ms both, fp16 batch 96 at 160x160 2.227 against 2.235.
 int row_blocks(int prec, long M, int C) {
-  const int CG = C < kCG ? C : kCG, groups = C / CG, rpi = 256 / (CG / prec_vw(prec));
+  const int CG = C < kCG ? C : kCG, groups = C / CG, rpi = 256 / (CG / prec_vw(prec)), cus = plan_cus();
   long b = (M + (long)rpi * kRowsU - 1) / ((long)rpi * kRowsU);
-  if (b * groups < 512) {
+  if (b * groups < 2 * cus) {
     // small tensors: fewer rows per thread, up to two blocks per CU
-    const long b1 = (M + rpi - 1) / rpi, lim = 512 / groups;
+    const long b1 = (M + rpi - 1) / rpi, lim = 2 * cus / groups;
     b = b1 < lim ? b1 : lim;
   }
-  const long cap = 2048 / groups;
+  const long cap = 8 * cus / groups;
   if (b > cap) b = cap;
   if (b < 1) b = 1;
   return (int)b * groups;
@@ -743,11 +749,11 @@ int bn_apply_pool_launch(int prec, const void* y, const BnSrc& b, void* pool, ui
   const int vw = prec_vw(prec);
   if (C > kMaxC || (long)N * H * W * (C / vw) >= (1l << 31)) return -1;  // 32-bit chunk indices
   const long total = (long)N * Ho * Wo * (C / vw);
-  const int blocks = stream_blocks(total);
+  const int blocks = std::min(stream_blocks(total), 8 * plan_cus());   // (see row_blocks)
   return with_prec(prec, [&](auto tag) {
     using T = decltype(tag);
-    hipLaunchKernelGGL(bn_apply_pool_kernel<T>, dim3(blocks < 2048 ? blocks : 2048), dim3(256), 0, s, (const T*)y, b,
-                       (T*)pool, arg, N, H, W, C, Ho, Wo);
+    hipLaunchKernelGGL(bn_apply_pool_kernel<T>, dim3(blocks), dim3(256), 0, s, (const T*)y, b, (T*)pool, arg, N, H, W,
+                       C, Ho, Wo);
     return ok();
   });
 }

@@ -3074,11 +3074,12 @@ int cu_count() {
   if (!n[dev] && hipDeviceGetAttribute(&n[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n[dev] = 0;
   return n[dev];
 }
-// Compute units that a choice of kernel is made for (256 without a GPU).
+}  // namespace
 int plan_cus() {
   const int n = cu_count();
   return n > 0 ? n : 256;
 }
+namespace {
 
 // A second K segment must have whole channel blocks, A2 shaped like A and
 // B2 [Cols][Cin], within the 32-bit buffer offsets.

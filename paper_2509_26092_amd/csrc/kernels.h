@@ -4,6 +4,9 @@
 
 namespace rn18 {
 
+// Compute units that a choice of kernel or grid is made for (256 without a GPU).
+int plan_cus();
+
 // ---------------------------------------------------------------------------
 // Implicit-GEMM convolution "gather" form, used for the forward pass and the
 // data gradient: C[m][col] = sum_{tap,ci} A[pixel(m,tap)][ci] * B[col][wtap][ci]
