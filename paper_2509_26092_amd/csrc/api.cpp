@@ -510,7 +510,7 @@ int build_plan(const Ctx& c, int N, int H, int W, Plan* pl, std::string* why) {
 // ----------------------------------------------------------------------------
 
 // Data gradient of a conv with input [N][H][W][Cin] and output [N][Ho][Wo][Cout].
-// mode: 0 store, 1 accumulate, 2 add masked residual (R, Rm).
+// mode: 0 store, 2 add masked residual (R, Rm).
 // dy2, wd2 (stride 2 only): the data gradient of a 1x1 stride-2 pad-0
 // projection of the same input ([N][Ho][Wo][Cout] and [Cin][Cout]) is added
 // inside the GEMM of parity phase (0,0), the only phase it reaches, so the
@@ -582,7 +582,6 @@ int launch_dgrad(int prec, const void* dy, const void* wd, void* dx, int N, int 
         g.A2 = dy2; g.B2 = wd2; g.K2 = Cout;
       }
       if (g.K == 0 && g.K2 == 0) {
-        if (mode == 1) continue;   // nothing to add
         g.nth = 1; g.ntw = 1;      // K = 0: the kernel writes acc = 0 (+ residual)
       }
       if (feed) {

@@ -476,12 +476,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_gather2_kernel(ConvGather
       float v[VW];
 #pragma unroll
       for (int e = 0; e < VW; ++e) v[e] = Ws[row * WSTR + cc * VW + e];
-      if (g.mode == 1) {
-        float o[VW];
-        unpack<T>(*(const uint4*)(Cg + off), o);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) v[e] += o[e];
-      } else if (g.mode == 2) {
+      if (g.mode == 2) {
         float rr[VW];
         unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
         const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];    // mask byte of this 16-byte chunk
@@ -529,8 +524,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_gather2_kernel(ConvGather
 }
 
 // Split-K reduce: the ksplit fp32 partial tiles of a gather launch summed in
-// range order, then the gather epilogue on the sum (mode 0 store, 1
-// accumulate, 2 masked residual; storage rounding). With g.stats set, the BN
+// range order, then the gather epilogue on the sum (mode 0 store, 2
+// masked residual; storage rounding). With g.stats set, the BN
 // partials are written per block of SK_ROWS rows as (rows, shift, sum of
 // v - shift, sum of squares), the shift being the block's first stored value
 // of the channel, like the gather kernel's entries per tile; with g.bstats
@@ -583,12 +578,7 @@ __global__ __launch_bounds__(256) void gather_splitk_reduce_kernel(ConvGather g)
       const int n = (int)g.fd_hw.div(m), rem = m - n * HWm;
       const int ii = (int)g.fd_w.div(rem), jj = rem - ii * g.Wm;
       const uint32_t off = ((uint32_t)((n * g.Hout + ii * g.os + g.oph) * g.Wout + jj * g.os + g.opw)) * g.Cols + col;
-      if (g.mode == 1) {
-        float o[VW];
-        unpack<T>(*(const uint4*)(Cg + off), o);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) v[e] += o[e];
-      } else if (g.mode == 2) {
+      if (g.mode == 2) {
         float rr[VW];
         unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
         const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];
@@ -977,12 +967,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, gather_occupancy(gather_rp_row
       float v[VW];
 #pragma unroll
       for (int e = 0; e < VW; ++e) v[e] = acc[i][p * TPC + e / 4][e % 4];
-      if (g.mode == 1) {
-        float o[VW];
-        unpack<T>(*(const uint4*)(Cg + off), o);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) v[e] += o[e];
-      } else if (g.mode == 2) {
+      if (g.mode == 2) {
         float rr[VW];
         unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
         const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];    // mask byte of this 16-byte chunk
@@ -1046,7 +1031,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, gather_occupancy(gather_rp_row
 //
 // A block walks tiles slot, slot + G, ...; the patch of the next channel block
 // or tile loads during the nine taps of the current one, in six parts, and the
-// output stores stay in flight during the next tile's taps. The grid is a
+// output stores stay in flight during the next tile's taps (an epilogue that
+// reads operands would wait for them: residuals and BN backward partials are
+// left to the gather tiles). The grid is a
 // multiple of the column tiles, so that a block keeps its columns and the BN
 // statistics accumulate per lane over its tiles: one entry per row of waves.
 //
@@ -1176,7 +1163,7 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
   T* __restrict__ Cg = (T*)g.C;
   const __amdgpu_buffer_rsrc_t rsC =
       __builtin_amdgcn_make_buffer_rsrc(g.C, 0, (uint32_t)((long)g.M * g.Cols * es), 0x00020000);
-  const bool stats = g.stats != nullptr, bstats = g.bstats != nullptr;
+  const bool stats = g.stats != nullptr;
   constexpr int CST = 16 * TPC;                    // channels between a lane's chunks
   const int col0 = n0 + wn * 64 + q4 * VW;
   float ssh[NC][VW], s1[NC][VW], s2[NC][VW];
@@ -1278,18 +1265,6 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
         float v[VW];
 #pragma unroll
         for (int e = 0; e < VW; ++e) v[e] = acc[i][p * TPC + e / 4][e % 4];
-        if (g.mode == 1) {
-          float o[VW];
-          unpack<T>(*(const uint4*)(Cg + off), o);
-#pragma unroll
-          for (int e = 0; e < VW; ++e) v[e] += o[e];
-        } else if (g.mode == 2) {
-          float rr[VW];
-          unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
-          const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];    // mask byte of this 16-byte chunk
-#pragma unroll
-          for (int e = 0; e < VW; ++e) v[e] += (mk >> e) & 1u ? rr[e] : 0.f;
-        }
         const uint4 pk = pack<T>(v);
         typedef int i32x4v_t __attribute__((ext_vector_type(4)));
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4v_t, pk), rsC, ok ? off * es : kOutOfRange, 0, 0);
@@ -1307,8 +1282,6 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
             s1[p][e] += d;
             s2[p][e] = __builtin_fmaf(d, d, s2[p][e]);
           }
-        } else if (bstats) {
-          if (ok) bwd_partial_add<T>(g, pk, off, col, s1[p], s2[p]);
         }
       }
     }
@@ -1323,7 +1296,7 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
     n = nn;
     i0 = ni0;
   }
-  if (stats || bstats) {
+  if (stats) {
     // one entry per row of waves: its pixels over all of the block's tiles
     const long entry = (long)(slot / h.tiles_n) * WGM + wm;
 #pragma unroll
@@ -1332,10 +1305,8 @@ __global__ __launch_bounds__(512, 2) void conv_halow_kernel(ConvHaloW h) {
       for (int e = 0; e < VW; ++e) {
         const float x1 = row16_sum(s1[p][e]), x2 = row16_sum(s2[p][e]);
         const int col = col0 + p * CST + e;
-        if (l16 == 0 && col < g.Cols) {
-          if (bstats) ((float2*)g.bstats)[entry * g.Cols + col] = make_float2(x1, x2);
-          else ((float4*)g.stats)[entry * g.Cols + col] = make_float4((float)rows_acc, ssh[p][e], x1, x2);
-        }
+        if (l16 == 0 && col < g.Cols)
+          ((float4*)g.stats)[entry * g.Cols + col] = make_float4((float)rows_acc, ssh[p][e], x1, x2);
       }
   }
   wait_vmcnt<0>();
@@ -1594,12 +1565,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, gather_occupancy(BM, BN, WGM * WGN,
         float v[VW];
 #pragma unroll
         for (int e = 0; e < VW; ++e) v[e] = Ws[row * WSTR + cc * VW + e];
-        if (g.mode == 1) {
-          float o[VW];
-          unpack<T>(*(const uint4*)(Cg + off), o);
-#pragma unroll
-          for (int e = 0; e < VW; ++e) v[e] += o[e];
-        } else if (g.mode == 2) {
+        if (g.mode == 2) {
           float rr[VW];
           unpack<T>(*(const uint4*)((const T*)g.R + off), rr);
           const uint32_t mk = ((const uint8_t*)g.Rm)[off / VW];  // mask byte of this 16-byte chunk
@@ -1701,6 +1667,7 @@ constexpr int HALO_PROWS = 640;  // patch pixels per half-patch buffer
 constexpr int HALO_WAVES = 8;    // waves per block = statistics entries per block
 constexpr int HALO_BM = 64 * HALO_WAVES;
 
+// MODE: 0 store, 2 add the masked residual.
 template <typename T, int MODE, bool STATS>
 __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo h) {
   constexpr int NW = HALO_WAVES, FM = 4, FN = 4;
@@ -1708,7 +1675,7 @@ __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo 
   constexpr int P_U4 = HALO_PROWS * 4;              // one half-patch buffer (64-byte rows)
   constexpr int PI = HALO_PROWS / 16 / NW;          // half-patch load instructions per wave (16 rows each)
   constexpr int BI = 9 * 64 / 8 / NW;               // weight load instructions per wave (8 rows each)
-  constexpr int kResidualLoads = MODE == 0 ? 0 : FM * FN * (MODE == 2 ? 2 : 1);   // per wave and tile
+  constexpr int kResidualLoads = MODE == 0 ? 0 : FM * FN * 2;   // per wave and tile
   static_assert(kResidualLoads < 64, "vmcnt range");
   __shared__ uint4 smem[B_U4 + 2 * P_U4];
   static_assert((B_U4 + 2 * P_U4) * 16 <= 163840, "LDS");
@@ -1776,7 +1743,7 @@ __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo 
   const uint32_t out_bytes = (uint32_t)((long)g.N * g.Hout * g.Wout * g.Cols * 2);
   const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(g.C, 0, out_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(g.mode == 1 || !g.R ? (const void*)g.C : g.R), 0, out_bytes, 0x00020000);
+      const_cast<void*>(g.R ? g.R : (const void*)g.C), 0, out_bytes, 0x00020000);
   // ReLU mask bytes of the residual: one byte per 8 output elements
   const __amdgpu_buffer_rsrc_t rsRm = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(g.Rm ? g.Rm : (const void*)g.C), 0, out_bytes / 16, 0x00020000);
@@ -1805,11 +1772,11 @@ __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo 
       okq[i] = q < npx;
       obase[i] = (uint32_t)((m0 + (okq[i] ? q : 0)) * g.Cols) + chl;
     }
-    // residual operands of modes 1 and 2, requested during the first half so
+    // residual operands of mode 2, requested during the first half so
     // that they have landed by the epilogue
     typedef int i32x2_t __attribute__((ext_vector_type(2)));
     i32x2_t ld0[MODE ? FM : 1][FN];
-    uint32_t ld1[MODE == 2 ? FM : 1][FN];
+    uint32_t ld1[MODE ? FM : 1][FN];
     floatx4_t acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -1838,9 +1805,8 @@ __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo 
             for (int j = 0; j < FN; ++j) {
               const uint32_t ob = okq[i] ? (obase[i] + j * 16) * 2 : kOutOfRange;
               ld0[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rsR, ob, 0, 0);
-              if constexpr (MODE == 2)
-                ld1[i][j] = __builtin_amdgcn_raw_buffer_load_b8(
-                    rsRm, okq[i] ? (obase[i] + j * 16) >> 3 : kOutOfRange, 0, 0);
+              ld1[i][j] = __builtin_amdgcn_raw_buffer_load_b8(
+                  rsRm, okq[i] ? (obase[i] + j * 16) >> 3 : kOutOfRange, 0, 0);
             }
         }
       } else if (tile + G < h.tiles) {
@@ -1899,12 +1865,8 @@ __global__ __launch_bounds__(64 * HALO_WAVES, 1) void conv_halo_kernel(ConvHalo 
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float rv = s16_to_f<T>((uint16_t)(e & 1 ? rw[e >> 1] >> 16 : rw[e >> 1] & 0xffffu));
-            if constexpr (MODE == 2) {
-              // this lane's 4 channels are the low or high half of the byte
-              x[e] += (ld1[i][j] >> ((chl & 4) + e)) & 1u ? rv : 0.f;
-            } else {
-              x[e] += rv;
-            }
+            // this lane's 4 channels are the low or high half of the byte
+            x[e] += (ld1[i][j] >> ((chl & 4) + e)) & 1u ? rv : 0.f;
           }
         }
         const uint2 pk = make_uint2(pack2<T>(x[0], x[1]), pack2<T>(x[2], x[3]));
@@ -3130,7 +3092,7 @@ int halo_rows(int prec, const ConvGather& g) {
     return 0;
   if (g.is != 1 || g.os != 1 || g.oph != 0 || g.opw != 0 || g.dhs != 1 || g.dws != 1) return 0;
   if (g.Hout != g.Hm || g.Wout != g.Wm || g.Hm < 1 || g.Wm < 1) return 0;
-  if (g.mode < 0 || g.mode > 2 || (g.mode != 0 && g.stats)) return 0;
+  if ((g.mode != 0 && g.mode != 2) || (g.mode != 0 && g.stats)) return 0;
   if ((long)g.N * g.Hin * g.Win * 128 >= (1l << 31) || (long)g.N * g.Hout * g.Wout * g.Cols >= (1l << 31)) return 0;
   // as many whole rows as fit 512 pixels and a 640-pixel patch; at least
   // 256 pixels per tile keeps the per-wave statistics entries (8 per block,
@@ -3202,7 +3164,6 @@ int launch_halo(const ConvGather& g0, int th, hipStream_t s) {
   constexpr int NT = 64 * HALO_WAVES;
   if (g0.mode == 0 && st) hipLaunchKernelGGL((conv_halo_kernel<T, 0, true>), dim3(grid), dim3(NT), 0, s, h);
   else if (g0.mode == 0) hipLaunchKernelGGL((conv_halo_kernel<T, 0, false>), dim3(grid), dim3(NT), 0, s, h);
-  else if (g0.mode == 1 && !st) hipLaunchKernelGGL((conv_halo_kernel<T, 1, false>), dim3(grid), dim3(NT), 0, s, h);
   else if (g0.mode == 2 && !st) hipLaunchKernelGGL((conv_halo_kernel<T, 2, false>), dim3(grid), dim3(NT), 0, s, h);
   else return -1;
   return hipGetLastError() == hipSuccess ? 0 : -4;
@@ -3211,8 +3172,10 @@ int launch_halo(const ConvGather& g0, int th, hipStream_t s) {
 
 // Image rows per tile of the wide halo kernel for a launch, or 0 when the
 // launch is not one it handles (16-bit, a 3x3 stride-1 pad-1 walk of whole
-// 128-byte channel blocks, more than 64 columns, output grid = row grid).
+// 128-byte channel blocks, more than 64 columns, output grid = row grid, an
+// epilogue that only stores and counts).
 int halow_rows(int prec, const ConvGather& g) {
+  if (g.mode != 0 || g.bstats) return 0;
   if (prec == PREC_F32 || g.Cin % 64 || g.Cols <= 64 || g.nth != 3 || g.ntw != 3 || g.KHW != 9 || g.KW != 3 ||
       g.K != 9 * g.Cin || g.K2)
     return 0;
@@ -3264,21 +3227,20 @@ int launch_halow(const ConvGather& g0, int th, hipStream_t s) {
 
 // Kernel configurations: id -> (BM, BN, waves along M, waves along N, waves
 // along K, stages, kind: 0 plain loop, 1 half-stage pipelined, 2 persistent).
+// Forcing an id without an entry leaves the choice automatic.
 #define RN18_GATHER_CONFIGS(X)                                                                                     \
-  X(1, 64, 32, 2, 2, 1, 3, 0) X(2, 64, 64, 2, 2, 1, 3, 0) X(3, 128, 64, 2, 2, 1, 2, 1)                             \
+  X(1, 64, 32, 2, 2, 1, 3, 0) X(2, 64, 64, 2, 2, 1, 3, 0)                                                          \
   X(4, 128, 128, 2, 4, 1, 2, 1) X(5, 256, 128, 4, 2, 1, 3, 1) X(6, 256, 128, 2, 2, 2, 3, 1)                        \
-  X(7, 256, 64, 4, 2, 1, 3, 1) X(8, 128, 128, 2, 4, 1, 4, 1) X(9, 64, 64, 2, 2, 1, 2, 1)                           \
+  X(8, 128, 128, 2, 4, 1, 4, 1) X(9, 64, 64, 2, 2, 1, 2, 1)                                                        \
   X(10, 64, 64, 2, 2, 1, 4, 1) X(11, 224, 128, 2, 2, 2, 3, 1) X(12, 448, 128, 4, 2, 1, 2, 1)                       \
   X(13, 128, 64, 2, 2, 1, 2, 0) X(14, 64, 64, 2, 2, 1, 2, 0) X(15, 256, 64, 4, 2, 1, 2, 0)                         \
   X(16, 128, 128, 2, 4, 1, 2, 0) X(17, 224, 256, 2, 4, 1, 2, 1) X(18, 512, 128, 4, 2, 1, 2, 1)                     \
-  X(19, 256, 256, 2, 4, 1, 2, 1) X(20, 64, 128, 1, 2, 2, 2, 1) X(21, 128, 128, 2, 2, 2, 4, 1)                      \
-  X(22, 256, 64, 4, 2, 1, 2, 1)                                                                                    \
+  X(19, 256, 256, 2, 4, 1, 2, 1) X(20, 64, 128, 1, 2, 2, 2, 1) X(22, 256, 64, 4, 2, 1, 2, 1)                       \
   X(35, 256, 64, 4, 2, 1, 2, 2) X(36, 128, 128, 2, 4, 1, 2, 2) X(37, 128, 64, 2, 2, 1, 2, 2)                       \
   X(38, 64, 64, 2, 2, 1, 2, 2) X(39, 256, 128, 4, 2, 1, 2, 2) X(40, 128, 128, 2, 2, 1, 2, 2)                       \
   X(41, 128, 256, 2, 4, 1, 2, 2) X(42, 128, 128, 2, 4, 1, 3, 2) X(43, 256, 64, 4, 2, 1, 3, 2)                      \
   X(44, 128, 64, 2, 2, 1, 3, 2)
-constexpr int kGatherCfgs = 44;
-constexpr int kGatherHaloW = 34;  // the wide halo kernel where it applies (ids 23..33 name the kernels of 3..13)
+constexpr int kGatherHaloW = 34;  // the wide halo kernel where it applies
 constexpr int kGatherHalo = 45;   // the halo kernels where they apply, else the automatic choice
 int g_gather_override = 0;
 
@@ -3288,6 +3250,11 @@ constexpr GatherCfg kGatherList[] = {
     RN18_GATHER_CONFIGS(RN18_X)
 #undef RN18_X
 };
+bool gather_listed(int id) {
+  for (const GatherCfg& c : kGatherList)
+    if (c.id == id) return true;
+  return false;
+}
 const GatherCfg& gather_entry(int id) {
   for (const GatherCfg& c : kGatherList)
     if (c.id == id) return c;
@@ -3325,10 +3292,9 @@ int gather_auto(int prec, const ConvGather& g);
 // Configuration of a launch: the forced one where it can run, else the
 // automatic choice.
 int gather_cfg(int prec, const ConvGather& g) {
-  int id = g_gather_override;
+  const int id = g_gather_override;
   if (id == 0 || id == kGatherHalo) return gather_auto(prec, g);
   if (id == kGatherHaloW) return halow_rows(prec, g) > 0 ? kGatherHaloW : gather_auto(prec, g);
-  if (id > 22 && id < kGatherHaloW) id -= 20;
   const GatherCfg& c = gather_entry(id);
   if (c.kind == 1) {
     if (!gather_uniform(g, 128 / prec_bytes(prec))) return gather_plain(g);
@@ -3349,7 +3315,7 @@ int gather_cfg(int prec, const ConvGather& g) {
 // large grids the wide halo kernel has the cheapest stages, the 224x256 and
 // 448x128 tiles read the fewest LDS bytes per MFMA but pay f per tile, and
 // two resident 128x128 blocks hide an epilogue with operands best (200704 x
-// 128, K 1152: 34 70, 16 81; with a residual 16 87, 34 93; 50176 x 256, K
+// 128, K 1152: 34 70, 16 81; with a residual 16 87; 50176 x 256, K
 // 2304: 12 60, 17 62, 16 75; 12544 x 512, K 4608: 11 61, 34 62, 16 71).
 // The deep rings (10, 8) are considered for grids of one round only: with more
 // rounds they took 17% and 7% more than the estimate (median of 88 and 76
@@ -3365,7 +3331,7 @@ constexpr GatherCost kCost16[] = {
     {5, 1, 7.5f, 9.f, {.71f}},                          {6, 1, 10.f, 9.f, {.64f}},
     {12, 1, 15.5f, 10.f, {1.05f}},                      {18, 1, 16.5f, 10.f, {1.16f}},
     {17, 1, 14.f, 6.f, {1.14f}},                        {19, 1, 16.f, 6.f, {1.16f}},
-    {kGatherHaloW, 1, 3.5f, 9.f, {.75f}},
+    {kGatherHaloW, 1, 3.5f, 0.f, {.75f}},
 };
 constexpr GatherCost kCost32[] = {
     {14, 5, 1.54f, 0.f, {1.36f}}, {9, 5, 1.6f, 0.f, {1.27f}}, {10, 2, 1.6f, 0.f, {1.30f}},
@@ -3809,8 +3775,10 @@ int conv_gather_split_count(int prec, const ConvGather& g) {
 // kernels and the split-K reduce (one launch of one sub-problem).
 bool conv_gather_bwd_ok(int prec, const ConvGather& g) {
   if (g.K2 || use_halo(prec, g) || use_halo16(prec, g)) return false;
-  const int id = gather_cfg(prec, g);
-  return id == kGatherHaloW || gather_entry(id).kind != 2;
+  static float partials;
+  ConvGather h = g;   // (as it would be launched, with partials to write)
+  h.bstats = &partials;
+  return gather_entry(gather_cfg(prec, h)).kind != 2;
 }
 
 int conv_gather_bwd_entries(int prec, const ConvGather& g) {
@@ -3852,7 +3820,7 @@ int conv_gather_split_override(int k) {
 
 int conv_gather_override(int id) {
   if (id < 0 || id > kGatherHalo) return -1;
-  g_gather_override = id;
+  g_gather_override = gather_listed(id) || id == kGatherHaloW || id == kGatherHalo ? id : 0;
   return 0;
 }
 

@@ -26,7 +26,7 @@ struct ConvGather {
   int dh0, dhs, dw0, dws;    // input offset of tap (th,tw): (dh0+th*dhs, dw0+tw*dws)
   int wkh0, wkhs, wkw0, wkws, KW, KHW;  // weight tap (wkh0+th*wkhs)*KW + wkw0+tw*wkws
   int K;                     // nth*ntw*Cin
-  int mode;                  // 0 store, 1 C += acc, 2 C = acc + (mask ? R : 0)
+  int mode;                  // 0 C = acc, 2 C = acc + (mask ? R : 0)
   FastDiv fd_hw, fd_w;       // division by Hm*Wm and by Wm (set by the launcher)
   float* stats;              // optional BN partials (rows, shift, sum, sum sq) [tiles_m][Cols][4] of the stored output
   const void* zero;          // 16-byte zero page (set by the launcher)
