@@ -245,9 +245,9 @@ hipEvent_t prof_event(Ctx* c) {
   return e;
 }
 
-// Start a timed launch group; returns its index or -1 when profiling is off.
+// Start a timed launch group (profiling is on: PROF_BEGIN); returns its index or -1.
 int prof_begin(Ctx* c, int cls, int layer, int tile, const char* name, double flops, double bytes) {
-    Ctx::ProfEv ev{cls, layer, tile, name, flops, bytes, prof_event(c), prof_event(c)};
+  Ctx::ProfEv ev{cls, layer, tile, name, flops, bytes, prof_event(c), prof_event(c)};
   if (!ev.a || !ev.b || hipEventRecord(ev.a, c->stream) != hipSuccess) return -1;
   c->prof.push_back(ev);
   return (int)c->prof.size() - 1;
@@ -478,12 +478,10 @@ int build_plan(const Ctx& c, int N, int H, int W, Plan* pl, std::string* why) {
     pl->bnst2 = alloc(mb);
     pl->part2 = alloc(mp);
   }
-  // (kernels address the split-K scratch with 64-bit offsets: not a tensor
-  // under the per-tensor limit)
   // Split-K scratch of one fixed size at every shape, so that the workspace
-  // stays linear in the batch (the memory model of Sec. 5.3). It holds the
-  // largest automatic split (3 ranges of 284 fp32 tiles of 128x128, 56 MB);
-  // the launcher cuts a larger forced split to fit. Kernels address it with
+  // stays linear in the batch (the memory model of Sec. 5.3). The automatic
+  // choice takes no more K ranges than fit it (at most 8, of launches of at most
+  // 255 tiles); the launcher cuts a larger forced split. Kernels address it with
   // 64-bit offsets: it is not a tensor under the per-tensor limit.
   pl->gsplit_bytes = kSplitScratchBytes;
   pl->gsplit = off;

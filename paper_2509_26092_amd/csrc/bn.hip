@@ -3,13 +3,13 @@
 //
 // Statistics are two-level and deterministic. Forward: the conv epilogue
 // writes per-tile partial sums of (v - shift) and (v - shift)^2 with a sample
-// of the channel as the shift (well conditioned when |mean| >> std), and a
-// finalize kernel merges the tiles in fp64. Backward: each block reduces a
+// of the channel as the shift (well conditioned when |mean| >> std), merged in
+// fp64 by the pass that applies them (bn_coefs). Backward: each block reduces a
 // contiguous range of rows to per-channel partial sums in fp32 (16-byte row
 // chunks read coalesced, then a fixed-order LDS reduction), combined in fp64.
 //
 // The elementwise passes (apply + ReLU + residual, backward apply) are 16-byte
-// HBM streams with the per-channel coefficients staged in LDS.
+// HBM streams; a thread keeps its channels' coefficients in registers.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -67,7 +67,7 @@ __device__ inline double block_sum_d(double v, double* sh) {
 // before it; above that bn_stats_tiles_reduce_kernel sums chunks of tiles
 // first (at most 16, so that a block reads at most 24 KB). A launch of a few
 // blocks costs 4-7 us beside its neighbours on MI355X: folding the finish took
-// the batch-64 step at 128x128 from 1.63 to 1.50 ms (evaluation of 80 images at 224x224: 0.89 to 0.83).
+// the batch-64 step at 128x128 from 1.63 to 1.50 ms.
 __device__ inline void bn_tile_sum(const float4& p, double K, double& N, double& S1, double& S2) {
   const double n = p.x, d = (double)p.y - K, s1 = p.z;
   N += n;

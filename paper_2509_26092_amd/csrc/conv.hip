@@ -655,9 +655,10 @@ constexpr int gather_occupancy(int bm, int bn, int nw, int stages) {
 // What bounds it: LDS. A 64x32 wave tile wants 192 bytes of operands a clock
 // per CU at the full MFMA rate, and reads deliver about 195 with nothing else
 // in the pipe; so the larger wave tiles where the grid fills them, and deep
-// rings where it does not. Forward or data gradient alone (us, two-stage
-// 128x128 tiles with reads before MFMAs first): 3136 x 512, K 4608, bf16 (64 x
-// 7 x 7): 38 -> 31; 32000 x 128, K 1152, fp32: 82 -> 74.
+// rings where it does not. Forward and data gradient of a layer called in turn
+// with its weight gradient (us, the plain loop's choice first): 3136 x 512, K
+// 4608, bf16 (64 x 7 x 7): 49 -> 42 and 40 -> 33; 32000 x 128, K 1152, fp32:
+// 95 -> 85 and 86 -> 77.
 //
 // Uniform row layout only (gather_uniform).
 // ---------------------------------------------------------------------------
@@ -1040,7 +1041,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, gather_occupancy(gather_rp_row
 // Operand order, weight rows, swizzles and the half-stage loop are those of
 // conv_gather_rp_kernel; so is the order of the K sum (channel blocks outer,
 // taps inner), and with it every result bit. 200704 x 128, K 1152, bf16 (256 x
-// 28 x 28), forward alone: 69 -> 65 us; the pure MFMA time is about 41.
+// 28 x 28), forward alone, the 128x128 tile first: 81 -> 73 us with operands
+// from HBM, 72 -> 69 with a new input, 79 -> 74 repeated; the pure MFMA time is
+// about 41.
 // ---------------------------------------------------------------------------
 struct ConvHaloW {
   ConvGather g;
@@ -3276,7 +3279,8 @@ int gather_plain(const ConvGather& g) {
 // Split-K for launches whose grid leaves CUs idle (fewer tiles than CUs:
 // small batches at the late stages, e.g. 1024 GEMM rows x 512 channels at
 // batch 64, 128x128 images): the K stages are cut into ranges of at least
-// kSplitMinStages, for about kSplitBlocks blocks in all. Measured on MI355X,
+// kSplitMinStages; how many, the estimate below decides, and for the layers it
+// does not choose for they make about kSplitBlocks blocks. Measured on MI355X,
 // whole training steps: batch 64 at 128x128 2.07 -> 1.87 ms, at 160x160
 // 2.27 -> 2.11 ms. Grids of 256..448 tiles, split, won alone but lost in the
 // step beside the weight-gradient stream (batch 256 at 224x224 +0.1 ms,
@@ -3310,19 +3314,22 @@ int gather_cfg(int prec, const ConvGather& g) {
 // The constants are fitted (within about 10%) to the launches of training steps
 // on MI355X, batch 64 to 256 at 128 to 224 pixels, each configuration forced
 // in turn: weights come cold from the Infinity Cache there, so deep rings win
-// on small grids (us, K 2304: 4096 x 256: 10 19, 14 32; 9600 x 256: 8 26, 14
-// 33; K 4608: 1024 x 512: 10 in two K ranges 24, five ranges of 14 28). On
-// large grids the wide halo kernel has the cheapest stages, the 224x256 and
-// 448x128 tiles read the fewest LDS bytes per MFMA but pay f per tile, and
-// two resident 128x128 blocks hide an epilogue with operands best (200704 x
-// 128, K 1152: 34 70, 16 81; with a residual 16 87; 50176 x 256, K
-// 2304: 12 60, 17 62, 16 75; 12544 x 512, K 4608: 11 61, 34 62, 16 71).
+// on small grids. Figures in us, a forward pass alone with operands from HBM
+// (and repeated, when they sit in L2): K 2304: 4096 x 256: 10 18 (22), 14 30
+// (22); 9600 x 256: 8 26 (29), 14 32 (29); K 4608: 3136 x 512: 10 36 (40), 14
+// 55 (46). Over 150 drawn layers a deep ring costs up to 8% where the layer is
+// only repeated, and saves 30-50% where its weights are cold. On large grids
+// the wide halo kernel has the cheapest stages, the 224x256 and 448x128 tiles
+// read the fewest LDS bytes per MFMA but pay f per tile, and two resident
+// 128x128 blocks hide an epilogue with operands best (200704 x 128, K 1152: 34
+// 73 (74), 16 81 (79); 50176 x 256, K 2304: 12 62 (60), 17 62 (58), 16 74 (73);
+// 12544 x 512, K 4608: 11 59 (62), 34 58 (62), 16 69 (63)).
 // The deep rings (10, 8) are considered for grids of one round only: with more
 // rounds they took 17% and 7% more than the estimate (median of 88 and 76
 // layers; 11160 x 320, K 2880: 10 55 us, 11 43, 16 47).
 // In fp32 the MFMAs bound every tile alike: the choice spreads the tiles most
 // evenly over the CUs, weighted by the measured share of the MFMA rate (f: with
-// one resident block, c[0]: with more). 36864 x 128, K 1152: 9 99 us, 16 147.
+// one resident block, c[0]: with more). 36864 x 128, K 1152: 9 105 us, 11 132.
 struct GatherCost { int id, bmax; float f, h, c[5]; bool one = false; };   // one: grids of a single round only
 constexpr GatherCost kCost16[] = {
     {14, 5, 1.f, 1.3f, {.62f, .66f, .68f, .72f, .88f}}, {10, 2, 1.5f, 1.9f, {.28f, .32f}, true},
